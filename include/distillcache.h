@@ -319,11 +319,9 @@ dc_status dc_decode_sample_evict(const dc_dims *dims, dc_kv *kv, dc_feat *feat,
  *   kept      [units][min(budget, len)] int32 indices into the row (the
  *             kept_out layout of dc_score_evict); needed for logp_out only
  *   logz_out, logp_out  [units] float64; either may be NULL
- * Computed by an O(len K) recursion, K = min(budget, len - budget), exact up
- * to rounding: the relative error of Z stays below about (K + len) 2^-24.
- * Scores whose spread divided by tau exceeds about 11000 fall outside exact
- * coverage (the smallest weights are clamped); a non-finite score or a kept
- * index outside [0, len) gives NaN for that unit.
+ * Computed in binary64 from the characteristic function of the subset size, exact
+ * up to rounding: about 1e-13 of the terms that are summed (sum |s| / tau).  A
+ * non-finite score or a kept index outside [0, len) gives NaN for that unit.
  * Workspace: dc_subset_log_prob_workspace_bytes(units, len, budget) bytes
  * (zero unless K > 4096).
  * Errors: DC_ERR_NULL (scores, or kept with logp_out), DC_ERR_SHAPE (units or

@@ -402,15 +402,9 @@ dc_status prep_logz(int32_t units, int32_t L, int32_t B, float tau, const float*
   z.nk = B < L ? B : L;
   z.logz = logz;
   z.logp = logp;
-  if (need) {
-    z.col_m = (float*)ws;
-    z.col_k = (int*)((char*)ws + (size_t)units * L * sizeof(float));
-  }
   z.units = units;
   z.L = L;
   z.B = B;
-  z.K = B >= L ? 0 : (B <= L - B ? B : L - B);
-  z.neg = B < L && L - B < B;
   z.tau = tau;
   return DC_OK;
 }
@@ -582,22 +576,12 @@ dc_status dc_score_evict_units(const dc_dims* dims, dc_kv* kv, dc_feat* feat, co
   }
   dc::LogzArgs z;
   if (logp_out) {
-    // K of any unit is at most min(budget, rows / 2): the kernel is chosen for that bound
     st = prep_logz(e.units, e.L, e.budget, gumbel->tau, scores_out, kept_out, nullptr, logp_out, ws,
                    ws_bytes, z);
     if (st != DC_OK) return st;
     z.unit_len = kv->unit_len;
     z.budgets = budgets;
     z.nk = e.ld_kept;
-    z.K = e.budget < e.L / 2 ? e.budget : e.L / 2;
-    if (z.K > dc::logz_band_entries()) {
-      // band history for that bound: 8 B per row, inside the row-key workspace
-      // the selection used (it is finished with it when the log-partition runs)
-      const size_t band = (size_t)e.units * e.L * (sizeof(float) + sizeof(int));
-      if (!ws || ws_bytes < band) return DC_ERR_WORKSPACE;
-      z.col_m = (float*)ws;
-      z.col_k = (int*)((char*)ws + (size_t)e.units * e.L * sizeof(float));
-    }
   }
   if (dc::launch_evict(e, dims->dtype, dims->head_dim, hip_stream) != 0) return DC_ERR_HIP;
   if (logp_out && dc::launch_logz(z, hip_stream) != 0) return DC_ERR_HIP;

@@ -95,11 +95,7 @@ struct LogzArgs {
   const int32_t* budgets;   // [units] budget of each unit or null: B for all
   double* logz;             // [units] or null
   double* logp;             // [units] or null (needs kept)
-  float* col_m;             // [units][L] band column (K > logz_band_entries()) or null
-  int* col_k;
   int units, L, B;
-  int K;                    // min(B, L - B); 0 when B >= L
-  int neg;                  // 1: the programme runs over exp(-r) (K = L - B < B)
   float tau;
 };
 
@@ -168,7 +164,6 @@ int launch_unit_len_add(int32_t* len, int units, int add, void* stream);
 int launch_unit_len_min(int32_t* len, const int32_t* budgets, int b, int units, void* stream);
 int launch_reinforce(const ReinforceArgs& a, void* stream);
 size_t logz_ws_bytes(int units, int L, int B);
-int logz_band_entries();
 int evict_max_len();
 size_t evict_ws_bytes(int units, int L);
 size_t evict_ext_ws_bytes(int units, int L);

@@ -94,6 +94,36 @@ def test_log_partition_workload_sizes(units, L, B_, tau):
         assert abs(lp[u] - refp) <= _logz_tol(L, B_), (u, lp[u] - refp)
 
 
+# The node count (a few rows, sigma^2 near 15 where it is largest, sigma near 0),
+# the chunk edges (4096 rows and one more, three chunks), both workgroup sizes, one
+# row kept or evicted, and rows thousands of units apart.
+EDGES = [(2, 2, 1, 1.0), (2, 3, 2, 1.0), (2, 4, 2, 1.0), (2, 5, 3, 4000.0), (2, 61, 30, 0.3),
+         (2, 64, 32, 1.0), (300, 67, 20, 2.0), (300, 257, 255, 1.0), (2, 513, 100, 3000.0),
+         (2, 1000, 4, 12.0), (1, 4096, 40, 1.0), (1, 4097, 4000, 1.0), (1, 8193, 60, 0.1),
+         (257, 300, 1, 1.0), (257, 300, 299, 800.0)]
+
+
+@pytest.mark.parametrize("units,L,B_,scale", EDGES)
+def test_log_partition_is_exact_to_binary64(units, L, B_, scale):
+    s = _scores(units, L, scale, step=3 * L, shift=0.5)
+    s[0, : L // 2] = s[0, 0]                                   # ties in the first unit
+    kept = np.stack([np.arange(u, u + B_) % L for u in range(units)]).astype(np.int32)
+    print(f"logz exact L={L} B={B_} units={units}", flush=True)
+    lz, lp = subset_log_prob(_dev(s), B_, 1.0, kept=_dev(kept, torch.int32))
+    torch.cuda.synchronize()
+    lz, lp = lz.cpu().numpy(), lp.cpu().numpy()
+    for u in sorted({0, 1, units - 1} & set(range(units))):
+        r = s[u].astype(np.float64)
+        K = min(B_, L - B_)
+        # log Z = sum r + log e_{L-B}(e^-r): the oracle's programme over K entries
+        ref = osmp.log_partition(r, B_) if B_ == K else r.sum() + osmp.log_partition(-r, K)
+        # binary64 rounding of L additions on either side, in units of what is summed
+        tol = 4 * (L + 64) * 2.0 ** -52 * (np.abs(r).sum() + L)
+        assert abs(lz[u] - ref) <= tol, (u, lz[u], ref, tol)
+        refp = r[kept[u]].sum() - ref
+        assert abs(lp[u] - refp) <= tol, (u, lp[u], refp, tol)
+
+
 def test_log_partition_special_rows():
     L = 400
     rows = [np.full(L, 0.37, np.float32),                               # all equal
