@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import policy as opol
 from oracle import unit as ounit
 from paper_2608_08878_amd import binding as B
 from paper_2608_08878_amd.buffers import DecodeBuffers, make_policy
@@ -162,3 +163,59 @@ def test_extended_policy_sampled_selection():
         post = H.download_unit(buf, u)
         ok, _, amb, flips = _sampled_check(s_or, pre[u]["pos"], post["pos"], wl.budget, 0.8, 31, u, 2)
         assert ok, (u, amb, flips)
+
+
+# The LayerNorm network's kernel: both padded widths with and without padded units,
+# items of 16 and of 64 rows (4096 items or more) with ragged tails, and weights,
+# gains and biases of any size behind its power-of-two scales.
+LN_CASES = [((128, 128), 5, 3, 70, "plain"), ((64, 64), 4, 3, 17, "plain"), ((100, 77), 5, 3, 130, "plain"),
+            ((48, 3), 5, 2, 300, "plain"), ((2, 128), 4, 2, 33, "plain"), ((128, 128), 5, 2100, 65, "plain"),
+            ((64, 40), 5, 2100, 100, "plain"), ((128, 128), 5, 3, 70, "w2 1e18"),
+            ((128, 128), 5, 3, 70, "w2 1e-18"), ((128, 128), 5, 3, 70, "gain 1e6"),
+            ((64, 64), 5, 3, 70, "bias 1e6"), ((128, 128), 5, 3, 70, "b2 1e12"), ((96, 96), 5, 3, 70, "w2 0")]
+
+
+@pytest.mark.parametrize("hidden,n_in,units,L,scale", LN_CASES)
+def test_layer_norm_network_scores(hidden, n_in, units, L, scale):
+    buf = DecodeBuffers(units, 1, 1, 1, 64, L + 1, "bf16", 8, 0.0, True, sigma=True)
+    buf.reserve_workspace(L + 1)
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    rnd = lambda: torch.rand((units, L + 1), generator=gen, device="cuda")  # noqa: E731
+    buf.alpha.copy_(rnd() * 0.01)
+    buf.den.copy_(rnd().double() + 0.01)
+    buf.num.copy_(buf.den * (4.0 + rnd().double()))
+    buf.vnorm.copy_(8.0 + 4.0 * rnd())
+    buf.sigma.copy_(rnd() * 1e-4)
+    buf.pos.copy_(torch.arange(L + 1, dtype=torch.int32, device="cuda").expand(units, L + 1))
+    buf.kv.len, buf.feat.next_pos = L, 2 * L
+    p, _ = _ext_params(n_in, hidden, True, 7)
+    (h1, h2), p = hidden, p.astype(np.float64)
+    o_b1 = h1 * n_in
+    o_w2 = o_b1 + 3 * h1
+    o_b2 = o_w2 + h2 * h1
+    if scale.startswith("w2"):
+        p[o_w2:o_b2] *= float(scale[3:])
+    if scale == "gain 1e6":
+        p[o_b1 + h1:o_w2] *= 1e6
+    if scale == "bias 1e6":                       # a common offset, which the mean takes out again
+        p[o_b1:o_b1 + h1] += 1e6
+    if scale == "b2 1e12":
+        p[o_b2:o_b2 + h2] *= 1e12
+    p = p.astype(np.float32)
+    params = torch.from_numpy(p).cuda()
+    scores = torch.empty((units, L), dtype=torch.float32, device="cuda")
+    print(f"LayerNorm network {hidden} {units} x {L} {scale}", flush=True)
+    buf.score_evict(make_policy(params, hidden, n_in=n_in, layer_norm=True), L, scores)
+    torch.cuda.synchronize()
+    g1, g2 = p[o_b1 + h1:o_b1 + 2 * h1].astype(np.float64), p[o_b2 + h2:o_b2 + 2 * h2].astype(np.float64)
+    be2, wo = p[o_b2 + 2 * h2:o_b2 + 3 * h2].astype(np.float64), p[o_b2 + 3 * h2:o_b2 + 4 * h2].astype(np.float64)
+    assert np.all(np.isfinite(g1))
+    for u in sorted({0, 1, units - 1}):
+        at = lambda t: t[u, :L].double().cpu().numpy()  # noqa: E731
+        x = [at(buf.alpha), at(buf.vnorm)] + ([at(buf.sigma)] if n_in == 5 else [])
+        x = np.stack(x + [at(buf.num) / at(buf.den), at(buf.pos) / (2 * L)], axis=1)
+        ref = opol.scores(p, x, hidden, layer_norm=True)
+        # 64 float32 roundings of the largest normalised unit, |z^| <= sqrt(h2)
+        tol = 64 * 2.0 ** -23 * (np.abs(wo) * (np.abs(g2) * np.sqrt(h2) + np.abs(be2))).sum() + 2.0 ** -20
+        err = np.abs(scores[u].double().cpu().numpy() - ref)
+        assert np.all(np.isfinite(err)) and err.max() <= tol, (u, err.max(), tol)
