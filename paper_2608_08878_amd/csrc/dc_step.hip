@@ -45,8 +45,33 @@ __device__ __forceinline__ float max16(float x) {
   return x;
 }
 
+// x + (x of lane l ^ 32), and l ^ 16, without the LDS pipe: after the swap of
+// two copies' halves one holds the lower lanes' values twice, the other the
+// upper ones'.
+__device__ __forceinline__ float add_xor32(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_xor16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Sum over the wave in butterfly order (32, 16, .. 1).  FAST: out of the LDS pipe.
+// Past the first two levels a value repeats every 8, 4, 2 lanes of a row, so a
+// rotation of the row by half a period is the butterfly's partner: the same bits.
+template <bool FAST>
 __device__ __forceinline__ float wave_sum(float x) {
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+  if constexpr (!FAST) {
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+    return x;
+  }
+  x = add_xor32(x);
+  x = add_xor16(x);
+  x += dpp<0x128>(x);    // row_ror:8
+  x += dpp<0x124>(x);
+  x += dpp<0x122>(x);
+  x += dpp<0x121>(x);
   return x;
 }
 
@@ -308,13 +333,13 @@ __device__ __forceinline__ void pass_p(float* sbuf, int n, const float (&M)[G], 
 }
 
 // Block sums of G-vectors (fixed order); stat: SNW * 2G + 2G floats of LDS.
-template <int G>
+template <int G, bool FAST>
 __device__ __forceinline__ void block_sum2(float (&x)[G], float (&y)[G], float* stat) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int j = 0; j < G; ++j) {
-    x[j] = wave_sum(x[j]);
-    y[j] = wave_sum(y[j]);
+    x[j] = wave_sum<FAST>(x[j]);
+    y[j] = wave_sum<FAST>(y[j]);
   }
   if (lane == 0) {
 #pragma unroll
@@ -339,24 +364,45 @@ __device__ __forceinline__ void block_sum2(float (&x)[G], float (&y)[G], float* 
 
 // pass B: rows [r0, r1), p from pbuf[(i - p0) * G + j]; per-wave partial output
 // o[j][e] for the lane's 8 dims (lanes 0..LPR-1 hold the wave total).
-template <int D, int G, int RS = G>
-__device__ __forceinline__ void pass_b(const DecodeArgs& a, int u, int r0, int r1,
-                                       const float* pbuf, int p0, float (&o)[G][8]) {
+// The first PF rows of a group are requested by pass_b_first, ahead of pass P
+// (they depend on nothing), so that their latency passes under it.
+constexpr int PF = 8;
+
+template <int D>
+struct VRows {                          // where unit u's value rows are
+  const char* vc;
+  const char* vn;
+  int newrow;
+  __device__ __forceinline__ VRows(const DecodeArgs& a, int u)
+      : vc((const char*)a.v + (size_t)u * a.cap * D * 2),
+        vn(a.append ? (const char*)a.v_new + (size_t)u * D * 2 : nullptr),
+        newrow(a.append ? len_old_of(a, u) : -1) {}
+  // rows past r1 load row r1 - 1 again (no divergent loads)
+  __device__ __forceinline__ uint4 load(int row, int r1, int lam) const {
+    const int rc = row < r1 ? row : r1 - 1;
+    return ldg16_nt((rc == newrow ? vn : vc + (size_t)rc * D * 2) + lam * 16);
+  }
+};
+
+template <int D>
+__device__ __forceinline__ void pass_b_first(const DecodeArgs& a, int u, int r0, int r1, uint4 (&vb)[PF]) {
   constexpr int LPR = MG<D>::LPR, NG = SNT / LPR;
-  constexpr int PF = 8;
+  const VRows<D> v(a, u);
+#pragma unroll
+  for (int p = 0; p < PF; ++p) vb[p] = v.load(r0 + (int)threadIdx.x / LPR + p * NG, r1, threadIdx.x % LPR);
+}
+
+template <int D, int G, bool FAST, int RS = G>
+__device__ __forceinline__ void pass_b(const DecodeArgs& a, int u, int r0, int r1,
+                                       const float* pbuf, int p0, uint4 (&vb)[PF], float (&o)[G][8]) {
+  constexpr int LPR = MG<D>::LPR, NG = SNT / LPR;
   const int tid = threadIdx.x, grp = tid / LPR, lam = tid % LPR;
-  const char* vc = (const char*)a.v + (size_t)u * a.cap * D * 2;
-  const char* vn = a.append ? (const char*)a.v_new + (size_t)u * D * 2 : nullptr;
-  const int newrow = a.append ? len_old_of(a, u) : -1;
+  const VRows<D> vr(a, u);
 #pragma unroll
   for (int j = 0; j < G; ++j)
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[j][e] = 0.0f;
-  // rows past r1 load row r1 - 1 again and are given weight 0 (no divergent loads)
-  auto load_row = [&](int row) {
-    const int rc = row < r1 ? row : r1 - 1;
-    return ldg16_nt((rc == newrow ? vn : vc + (size_t)rc * D * 2) + lam * 16);
-  };
+  // (rows past r1 are given weight 0)
   auto accumulate = [&](int row, const uint4& vv) {
     const bool ok = row < r1;
     const int rc = ok ? row : r1 - 1;
@@ -387,9 +433,6 @@ __device__ __forceinline__ void pass_b(const DecodeArgs& a, int u, int r0, int r
   // other half's loads are still outstanding; the last iters % PF rows are
   // consumed after the loop without new loads.
   constexpr int HF = PF / 2;
-  uint4 vb[PF];
-#pragma unroll
-  for (int p = 0; p < PF; ++p) vb[p] = load_row(r0 + grp + p * NG);
   const int full = iters / PF;
   for (int f = 0; f < full; ++f) {
 #pragma unroll
@@ -397,7 +440,7 @@ __device__ __forceinline__ void pass_b(const DecodeArgs& a, int u, int r0, int r
 #pragma unroll
       for (int q = 0; q < HF; ++q) accumulate(r0 + grp + (f * PF + h * HF + q) * NG, vb[h * HF + q]);
 #pragma unroll
-      for (int q = 0; q < HF; ++q) vb[h * HF + q] = load_row(r0 + grp + ((f + 1) * PF + h * HF + q) * NG);
+      for (int q = 0; q < HF; ++q) vb[h * HF + q] = vr.load(r0 + grp + ((f + 1) * PF + h * HF + q) * NG, r1, lam);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -405,11 +448,20 @@ __device__ __forceinline__ void pass_b(const DecodeArgs& a, int u, int r0, int r
   for (int p = 0; p < PF; ++p)
     if (full * PF + p < iters) accumulate(r0 + grp + (full * PF + p) * NG, vb[p]);
 #pragma unroll
-  for (int off = LPR; off < 64; off *= 2)
+  for (int j = 0; j < G; ++j)
 #pragma unroll
-    for (int j = 0; j < G; ++j)
+    for (int e = 0; e < 8; ++e) {
+      float x = o[j][e];
+      if constexpr (!FAST) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[j][e] = o[j][e] + __shfl_xor(o[j][e], off);
+        for (int off = LPR; off < 64; off *= 2) x = x + __shfl_xor(x, off);
+        o[j][e] = x;
+        continue;
+      }
+      if constexpr (LPR == 8) x += dpp<0x128>(x);      // lane ^ 8: the row rotated by eight
+      x = add_xor16(x);
+      o[j][e] = add_xor32(x);
+    }
 }
 
 // Norm of the appended value row (every thread receives it through LDS).
@@ -524,7 +576,15 @@ struct RowStride {
 // kernels serve it).  The compaction plan sits in the free half of the rows'
 // LDS slots beside the keys (move j beside row j's key: at most L / 2 moves,
 // however many rows the unit evicts), so it needs RS >= 4 (G >= 4).
-template <int D, int G, bool FEAT, bool EVICT, bool SIG = false, bool SMP = false, bool RAG = false>
+// EARLY: value rows are requested ahead of pass P, the state ahead of the output
+// combination, and the sums stay out of the LDS pipe, since a step waits for its
+// own chain of passes.  Measured per step, off -> on: 2304 units of 187 rows 81.1 ->
+// 73.0 us, 2048 of 513 139.4 -> 131.9 (G = 8: 232.8 -> 215.0), 2048 of 1025 236.4 ->
+// 232.8, 1024 of 2049 224.7 -> 223.0, of 3342 368.1 -> 367.9, 256 of 1025 37.5 -> 35.4,
+// 8 of 1025 28.2 -> 27.4; G = 8: 1024 of 2049 295 -> 284.  Where just two workgroups per CU cover each other's
+// waits, and on long rows, it costs instead: 512 of 1025 60.0 -> 60.7 us, 4096 of
+// 4097 1701 -> 1712.  The bits are the same.
+template <int D, int G, bool FEAT, bool EVICT, bool SIG, bool SMP, bool RAG, bool EARLY>
 __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArgs a, EvictArgs e) {
   static_assert(!SIG || (FEAT && !EVICT), "sigma is stored by the decode-only variant");
   static_assert(!SMP || (EVICT && RowStride<G>::RS >= 4), "sampling keeps the score beside the key");
@@ -559,20 +619,43 @@ __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArg
     pass_a<D, G, FEAT, true, RS>(a, u, 0, L, sbuf, nullptr, 0, qa, retire, rs, mrun, zr, nr);
     block_max<G>(mrun, stat, M);
   }
+  uint4 vb[PF];
+  if constexpr (EARLY) pass_b_first<D>(a, u, 0, L, vb);
   {
     float ls[G], us[G];
     pass_p<G, RS>(sbuf, L, M, ls, us);
     __syncthreads();
-    block_sum2<G>(ls, us, stat);
+    block_sum2<G, EARLY>(ls, us, stat);
 #pragma unroll
     for (int j = 0; j < G; ++j) {
       invl[j] = 1.0f / ls[j];
       H[j] = __logf(ls[j]) - us[j] * invl[j];
     }
   }
+  // the feature state of pass A's 64-row groups (see the feature pass); the
+  // first group's is requested before the outputs are combined
+  const int ngrp = (L + 63) / 64;
+  const int ngw = wave < ngrp ? (ngrp - 1 - wave) / SNW + 1 : 0;
+  struct Row {
+    float al, vn;
+    double nu, de;
+    int32_t p;
+  };
+  auto load_row = [&](int k, Row& x) {
+    const int r = 64 * (wave + SNW * k) + lane;
+    const size_t gi = ub + (r < L ? r : L - 1);
+    x.al = a.alpha[gi];
+    x.nu = a.num[gi];
+    x.de = a.den[gi];
+    x.p = a.pos[gi];
+    x.vn = a.vnorm[gi];
+  };
+  Row cur = {};
   {
     float o[G][8];
-    pass_b<D, G, RS>(a, u, 0, L, sbuf, 0, o);
+    if constexpr (!EARLY) pass_b_first<D>(a, u, 0, L, vb);
+    pass_b<D, G, EARLY, RS>(a, u, 0, L, sbuf, 0, vb, o);
+    if (FEAT && EARLY && ngw > 0) load_row(0, cur);
     // tree over the waves through SNW/2 partial slots
     if (wave >= SNW / 2 && lane < LPR) {
 #pragma unroll
@@ -612,24 +695,8 @@ __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArg
     // group's state is requested before the current one is updated; in full
     // groups every load and store is unconditional, only the unit's partial last
     // group (one wave) guards its stores.
-    const int ngrp = (L + 63) / 64;
-    const int ngw = wave < ngrp ? (ngrp - 1 - wave) / SNW + 1 : 0;
     const bool part = ngw > 0 && wave + SNW * (ngw - 1) == ngrp - 1 && (L & 63) != 0;
     const int nfull = ngw - (part ? 1 : 0);
-    struct Row {
-      float al, vn;
-      double nu, de;
-      int32_t p;
-    };
-    auto load_row = [&](int k, Row& x) {
-      const int r = 64 * (wave + SNW * k) + lane;
-      const size_t gi = ub + (r < L ? r : L - 1);
-      x.al = a.alpha[gi];
-      x.nu = a.num[gi];
-      x.de = a.den[gi];
-      x.p = a.pos[gi];
-      x.vn = a.vnorm[gi];
-    };
     auto update = [&](int k, const Row& x, bool guard) {
       const int r = 64 * (wave + SNW * k) + lane;
       const bool valid = r < L;
@@ -684,8 +751,8 @@ __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArg
       }
     };
     if (ngw > 0) {
-      Row cur, nxt;
-      load_row(0, cur);
+      Row nxt;
+      if constexpr (!EARLY) load_row(0, cur);
       for (int k = 0; k < nfull; ++k) {
         load_row(k + 1 < ngw ? k + 1 : k, nxt);
         update(k, cur, false);
@@ -790,12 +857,14 @@ __global__ void __launch_bounds__(SNT) stepc_ab_kernel(DecodeArgs a) {
   const float* src = a.ws_s + ((size_t)u * a.lmax + r0) * G;
   for (int t = tid; t < n * G; t += SNT) pbuf[t] = src[t];
   __syncthreads();
+  uint4 vb[PF];
+  pass_b_first<D>(a, u, r0, r1, vb);
   float ls[G], us[G];
   pass_p<G>(pbuf, n, M, ls, us);
   __syncthreads();
-  block_sum2<G>(ls, us, stat);
+  block_sum2<G, true>(ls, us, stat);
   float o[G][8];
-  pass_b<D, G>(a, u, r0, r1, pbuf, r0, o);
+  pass_b<D, G, true>(a, u, r0, r1, pbuf, r0, vb, o);
   if (lane < LPR) {
 #pragma unroll
     for (int j = 0; j < G; ++j)
@@ -953,18 +1022,24 @@ static int launch_step_t(const DecodeArgs& a, const EvictArgs* e, bool feat, boo
       hipLaunchKernelGGL(kern, dim3(a.units), dim3(SNT), lds, s, a, ee);
     };
     // (the fused evicting variants serve the one-hidden-layer four-input policy)
-    if (!feat) pick(step_unit_kernel<D, G, false, false>);
+    // one workgroup per CU at most (G > 4: its registers allow no second), or more
+    // rounds than one of not too long rows
+    // (step_unit_kernel's comment has both sides)
+    const bool early = G > 4 || a.units <= 256 || a.L <= 512 || (a.units > 512 && a.L <= 3584);
+#define DC_STEP(...) do { if (early) pick(step_unit_kernel<D, G, __VA_ARGS__, true>); else pick(step_unit_kernel<D, G, __VA_ARGS__, false>); } while (0)
+    if (!feat) DC_STEP(false, false, false, false, false);
     else if (e && e->sample) {
-      if constexpr (RowStride<G>::RS >= 4) pick(step_unit_kernel<D, G, true, true, false, true>);
+      if constexpr (RowStride<G>::RS >= 4) DC_STEP(true, true, false, true, false);
       else return (int)hipErrorInvalidValue;     // the caller takes the separate path
     }
     else if (e && a.unit_len) {
-      if constexpr (RowStride<G>::RS >= 4) pick(step_unit_kernel<D, G, true, true, false, false, true>);
+      if constexpr (RowStride<G>::RS >= 4) DC_STEP(true, true, false, false, true);
       else return (int)hipErrorInvalidValue;     // the caller takes the separate path
     }
-    else if (e) pick(step_unit_kernel<D, G, true, true>);
-    else if (a.sigma) pick(step_unit_kernel<D, G, true, false, true>);
-    else pick(step_unit_kernel<D, G, true, false>);
+    else if (e) DC_STEP(true, true, false, false, false);
+    else if (a.sigma) DC_STEP(true, false, true, false, false);
+    else DC_STEP(true, false, false, false, false);
+#undef DC_STEP
   } else {
     // every slice of one pass before the next (stream order)
     for_grid_y(a.units, [&](int y0, int ny) {

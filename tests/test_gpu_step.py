@@ -728,3 +728,33 @@ def test_chunked_step_across_head_groups_and_dims(n_q, n_kv, d):
     for u in range(U):
         s_or = ounit.scores(sts[u], pnp, wl.hidden)
         _check_evict(wl, wl.budget, pre[u], sc[u], kp[u], H.download_unit(buf, u), s_or, ("c", u))
+
+
+@pytest.mark.parametrize("D,G", [(128, 4), (64, 4), (128, 1), (64, 2)])
+def test_early_requests_keep_the_bits(D, G):
+    """257..512 units of more than 512 rows (G <= 4) take the kernel without early requests, 16 of the
+    same units the one with them: outputs, scores, slots and state are the same bits."""
+    U, n, budget = 260, 600, 560
+    gen = torch.Generator(device="cuda").manual_seed(D + G)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    k, v, q, kn, vn = rnd(U, n + 2, D), rnd(U, n + 2, D), rnd(2, U, G, D), rnd(2, U, D), rnd(2, U, D)
+    params = torch.randn(32 * 4 + 32 + 32 + 1, generator=gen, device="cuda") * 0.1
+    got = []
+    for units in (U, 16):
+        buf = DecodeBuffers(units, 1, G, 1, D, n + 2, "bf16", 1)
+        buf.k.copy_(k[:units])
+        buf.v.copy_(v[:units])
+        buf.feat_init(n, 0)
+        out, scores = torch.empty_like(q[:, :units]), torch.empty((units, n + 2), device="cuda")
+        kept = torch.empty((units, budget), dtype=torch.int32, device="cuda")
+        print(f"early requests D={D} G={G} units={units}", flush=True)
+        buf.decode_step(q[0, :units].contiguous(), kn[0, :units], vn[0, :units], out[0])
+        # (a window of one step: this one retires the first)
+        buf.decode_evict(make_policy(params, (32,)), budget, q[1, :units].contiguous(), kn[1, :units], vn[1, :units],
+                         out[1], scores, kept)
+        torch.cuda.synchronize()
+        got.append([out, scores, kept] + [x[:, :budget] for x in (buf.k, buf.v, buf.alpha, buf.num, buf.den, buf.pos,
+                                                                  buf.vnorm)])
+    for i, (a, b) in enumerate(zip(*got)):
+        a = a[:, :16] if i == 0 else a[:16]
+        assert torch.equal(a, b), i
