@@ -379,10 +379,29 @@ dc_status ragged_after_decode(const dc_kv* kv, const dc::DecodeArgs& a, void* st
   if (!kv->unit_len || !a.append) return DC_OK;
   return dc::launch_unit_len_add(kv->unit_len, a.units, 1, stream) ? DC_ERR_HIP : DC_OK;
 }
+// add: rows appended that the lengths do not count yet
 dc_status ragged_after_evict(const dc_kv* kv, const dc::EvictArgs& e, const int32_t* budgets,
-                             int bmax, void* stream) {
-  if (!kv->unit_len || (!budgets && !e.evict)) return DC_OK;
-  return dc::launch_unit_len_min(kv->unit_len, budgets, bmax, e.units, stream) ? DC_ERR_HIP : DC_OK;
+                             int bmax, void* stream, int add = 0) {
+  if (!kv->unit_len || (!budgets && !e.evict && !add)) return DC_OK;
+  return dc::launch_unit_len_min(kv->unit_len, budgets, bmax, add, e.units, stream) ? DC_ERR_HIP : DC_OK;
+}
+
+// A decode step and its selection in separate launches.  The chunked bf16 step
+// scores with its features when the policy is the one-hidden-layer one; then the
+// lengths of a ragged cache are brought up to date once, after the selection
+// (e.len_add; the caller passes it to ragged_after_evict), else after the decode.
+dc_status decode_then_evict(const dc_dims* dims, const dc_kv* kv, const dc::DecodeArgs& a,
+                            dc::EvictArgs& e, bool split, void* stream) {
+  const int G = group_of(dims), D = dims->head_dim;
+  if (dims->dtype == DC_BF16 && split && !e.ext) {
+    if (dc::launch_step(a, &e, D, G, true, true, stream) != 0) return DC_ERR_HIP;
+    e.len_add = kv->unit_len ? a.append : 0;
+    return dc::launch_select_keys(e, dc::step_keys(a), a.lmax, D, stream) ? DC_ERR_HIP : DC_OK;
+  }
+  const dc_status st = launch_decode_any(dims, a, true, split, stream);
+  if (st != DC_OK) return st;
+  if (ragged_after_decode(kv, a, stream) != DC_OK) return DC_ERR_HIP;
+  return dc::launch_evict(e, dims->dtype, D, stream) ? DC_ERR_HIP : DC_OK;
 }
 
 // Validate a log-partition call and fill its arguments.
@@ -539,16 +558,15 @@ dc_status dc_decode_sample_evict(const dc_dims* dims, dc_kv* kv, dc_feat* feat,
   if (fused) {
     if (dc::launch_step(a, &e, D, G, true, false, hip_stream) != 0) return DC_ERR_HIP;
   } else {
-    st = launch_decode_any(dims, a, true, split, hip_stream);
+    st = decode_then_evict(dims, kv, a, e, split, hip_stream);
     if (st != DC_OK) return st;
-    if (ragged_after_decode(kv, a, hip_stream) != DC_OK) return DC_ERR_HIP;
-    if (dc::launch_evict(e, dims->dtype, D, hip_stream) != 0) return DC_ERR_HIP;
   }
   if (logp_out) {
     z.unit_len = kv->unit_len;
+    z.len_add = e.len_add;
     if (dc::launch_logz(z, hip_stream) != 0) return DC_ERR_HIP;
   }
-  if (ragged_after_evict(kv, e, nullptr, e.budget, hip_stream) != DC_OK) return DC_ERR_HIP;
+  if (ragged_after_evict(kv, e, nullptr, e.budget, hip_stream, e.len_add) != DC_OK) return DC_ERR_HIP;
   commit_decode(kv, feat, a, dims->ent_window);
   kv->len = e.budget;
   return DC_OK;
@@ -614,10 +632,8 @@ dc_status dc_decode_evict_units(const dc_dims* dims, dc_kv* kv, dc_feat* feat,
   const int Lf = dc::step_ragged_rows(G, D);
   if (e.ext || feat->sigma || Lf < 1 || (int)units_of(dims) < FEW_UNITS) {
     // the two-call route: chunked decode, then the per-unit selection
-    st = launch_decode_any(dims, a, true, split, hip_stream);
+    st = decode_then_evict(dims, kv, a, e, split, hip_stream);
     if (st != DC_OK) return st;
-    if (ragged_after_decode(kv, a, hip_stream) != DC_OK) return DC_ERR_HIP;
-    if (dc::launch_evict(e, dims->dtype, D, hip_stream) != 0) return DC_ERR_HIP;
   } else {
     dc::DecodeArgs af = a;
     af.L = a.L < Lf ? a.L : Lf;     // the rows one workgroup serves (LDS); longer units leave
@@ -625,21 +641,17 @@ dc_status dc_decode_evict_units(const dc_dims* dims, dc_kv* kv, dc_feat* feat,
     ef.L = a.L;                     // row stride of scores_out
     if (dc::launch_step(af, &ef, D, G, true, false, hip_stream) != 0) return DC_ERR_HIP;
     if (a.L > af.L) {
-      // the longer units: chunked decode, then their scoring and selection
+      // the longer units: chunked decode with their scores, then their selection
       dc::DecodeArgs ac = a;
       ac.fused_rows = af.L;
-      st = launch_decode_any(dims, ac, true, true, hip_stream);
-      if (st != DC_OK) return st;
-    }
-    // every kernel of the decode has read the old lengths
-    if (ragged_after_decode(kv, a, hip_stream) != DC_OK) return DC_ERR_HIP;
-    if (a.L > af.L) {
       dc::EvictArgs el = e;
       el.fused_rows = af.L;
-      if (dc::launch_evict(el, dims->dtype, D, hip_stream) != 0) return DC_ERR_HIP;
+      st = decode_then_evict(dims, kv, ac, el, true, hip_stream);
+      if (st != DC_OK) return st;
     }
+    e.len_add = a.append;             // every kernel has read the old lengths
   }
-  if (ragged_after_evict(kv, e, budgets, e.budget, hip_stream) != DC_OK) return DC_ERR_HIP;
+  if (ragged_after_evict(kv, e, budgets, e.budget, hip_stream, e.len_add) != DC_OK) return DC_ERR_HIP;
   commit_decode(kv, feat, a, dims->ent_window);
   kv->len = e.budget;
   return DC_OK;
@@ -685,12 +697,10 @@ dc_status dc_decode_evict(const dc_dims* dims, dc_kv* kv, dc_feat* feat, const d
   if (fused) {
     if (dc::launch_step(a, &e, D, G, true, false, hip_stream) != 0) return DC_ERR_HIP;
   } else {
-    st = launch_decode_any(dims, a, true, split, hip_stream);
+    st = decode_then_evict(dims, kv, a, e, split, hip_stream);
     if (st != DC_OK) return st;
-    if (ragged_after_decode(kv, a, hip_stream) != DC_OK) return DC_ERR_HIP;
-    if (dc::launch_evict(e, dims->dtype, D, hip_stream) != 0) return DC_ERR_HIP;
   }
-  if (ragged_after_evict(kv, e, nullptr, e.budget, hip_stream) != DC_OK) return DC_ERR_HIP;
+  if (ragged_after_evict(kv, e, nullptr, e.budget, hip_stream, e.len_add) != DC_OK) return DC_ERR_HIP;
   commit_decode(kv, feat, a, dims->ent_window);
   kv->len = e.budget;
   return DC_OK;

@@ -140,15 +140,36 @@ __global__ void identity_kept_kernel(int32_t* kept, int units, int L) {
 
 int evict_max_len() { return MAX_LEN; }
 
+// moves: min(L - B, B); per-unit budgets: at most min(L / 2, the largest budget)
+static int moves_bound(const EvictArgs& a) {
+  const int E = a.L - a.budget;
+  if (a.unit_len || a.budgets) return a.L / 2 < a.budget ? a.L / 2 : a.budget;
+  return a.evict ? (E < a.budget ? E : a.budget) : 0;
+}
+static int move_ints(int nmv) { return (2 * (nmv > 0 ? nmv : 1) + 3) / 4 * 4; }
+
+// One workgroup per unit selects from the row keys and compacts.
+template <int DTYPE, int D>
+static int launch_select_t(const EvictArgs& a, const uint64_t* keys, int kstride, int nmv, hipStream_t s) {
+  const size_t dyn = (size_t)a.mv_ints * sizeof(int);
+  if (a.evict || a.unit_len || a.budgets) {
+    const bool wide = nmv >= 4096;
+    auto k = wide ? select_kernel<DTYPE, D, ENT> : select_kernel<DTYPE, D, 512>;
+    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    hipLaunchKernelGGL(k, dim3(a.units), dim3(wide ? ENT : 512), dyn, s, a, keys, kstride);
+  } else if (a.kept_out) {
+    hipLaunchKernelGGL(identity_kept_kernel, dim3(1024), dim3(256), 0, s, a.kept_out, a.units, a.L);
+  }
+  return (int)hipGetLastError();
+}
+
 template <int DTYPE, int D>
 static int launch_evict_t(const EvictArgs& a, uint64_t* ws_keys, hipStream_t s) {
   const bool rg = a.unit_len || a.budgets;
   if (!a.evict && !rg && !a.scores_out && !a.kept_out) return 0;
-  // moves: min(L - B, B); per-unit budgets: at most min(L / 2, the largest budget)
-  const int E = a.L - a.budget;
-  const int nmv = rg ? (a.L / 2 < a.budget ? a.L / 2 : a.budget) : a.evict ? (E < a.budget ? E : a.budget) : 0;
+  const int nmv = moves_bound(a);
   EvictArgs b = a;
-  b.mv_ints = (2 * (nmv > 0 ? nmv : 1) + 3) / 4 * 4;
+  b.mv_ints = move_ints(nmv);
   const size_t dyn = (size_t)b.mv_ints * sizeof(int);
   const int kstride = (a.L + ENT - 1) / ENT * ENT;
   const bool ragged = a.unit_len || a.budgets;
@@ -179,16 +200,17 @@ static int launch_evict_t(const EvictArgs& a, uint64_t* ws_keys, hipStream_t s) 
       else hipLaunchKernelGGL(score_kernel, grid, dim3(256), 0, s, c, ws_keys, kstride);
     });
   }
-  if (a.evict || ragged) {
-    const bool wide = nmv >= 4096;
-    auto k = wide ? select_kernel<DTYPE, D, ENT> : select_kernel<DTYPE, D, 512>;
-    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
-    hipLaunchKernelGGL(k, dim3(a.units), dim3(wide ? ENT : 512), dyn, s, b, (const uint64_t*)ws_keys,
-                       kstride);
-  } else if (a.kept_out) {
-    hipLaunchKernelGGL(identity_kept_kernel, dim3(1024), dim3(256), 0, s, a.kept_out, a.units, a.L);
-  }
-  return (int)hipGetLastError();
+  return launch_select_t<DTYPE, D>(b, ws_keys, kstride, nmv, s);
+}
+
+int launch_select_keys(const EvictArgs& a, const uint64_t* keys, int kstride, int D, void* stream) {
+  const int nmv = moves_bound(a);
+  EvictArgs b = a;
+  b.mv_ints = move_ints(nmv);
+  hipStream_t s = (hipStream_t)stream;
+  if (D == 128) return launch_select_t<1, 128>(b, keys, kstride, nmv, s);
+  if (D == 64) return launch_select_t<1, 64>(b, keys, kstride, nmv, s);
+  return (int)hipErrorInvalidValue;
 }
 
 int launch_evict(const EvictArgs& a, int dtype, int D, void* stream) {

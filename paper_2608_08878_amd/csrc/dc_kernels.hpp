@@ -59,6 +59,7 @@ struct EvictArgs {
   float* vnorm;
   float* sigma;         // [units][cap] or null (moved with the rows; read by 5-input policies)
   const int32_t* unit_len;  // [units] rows of each unit (ragged caches) or null (L rows each)
+  int len_add;              // rows appended since unit_len was last brought up to date
   const int32_t* budgets;   // [units] budget of each unit, or null (budget for all)
   int ld_kept;          // row stride of kept_out (the budget, or its bound for per-unit budgets)
   const float* params;
@@ -92,6 +93,7 @@ struct LogzArgs {
   const int32_t* kept;      // [units][nk] kept rows (indices into the scores) or null (row stride nk)
   int nk;                   // min(B, L)
   const int32_t* unit_len;  // [units] rows of each unit (ragged) or null: L for all
+  int len_add;              // rows appended since unit_len was last brought up to date
   const int32_t* budgets;   // [units] budget of each unit or null: B for all
   double* logz;             // [units] or null
   double* logp;             // [units] or null (needs kept)
@@ -159,9 +161,11 @@ bool decode_fits_lds(int L, int G, int D);
 int decode_chunk_rows();
 int launch_evict(const EvictArgs& a, int dtype, int D, void* stream);
 int launch_logz(const LogzArgs& a, void* stream);
-// Ragged caches: len[u] += add, or len[u] = min(len[u], budgets ? budgets[u] : b).
+// The selection alone, from row keys that stepc_d_kernel formed (bf16).
+int launch_select_keys(const EvictArgs& a, const uint64_t* keys, int kstride, int D, void* stream);
+// Ragged caches: len[u] += add, or len[u] = min(len[u] + add, budgets ? budgets[u] : b).
 int launch_unit_len_add(int32_t* len, int units, int add, void* stream);
-int launch_unit_len_min(int32_t* len, const int32_t* budgets, int b, int units, void* stream);
+int launch_unit_len_min(int32_t* len, const int32_t* budgets, int b, int add, int units, void* stream);
 int launch_reinforce(const ReinforceArgs& a, void* stream);
 size_t logz_ws_bytes(int units, int L, int B);
 int evict_max_len();
@@ -174,9 +178,11 @@ int launch_kl_pack(const void* w, void* packed, int hidden, int vocab, void* str
 int kl_static_scratch(float** out);
 int launch_global_alpha(const GlobalAlphaArgs& a, void* stream);
 int global_alpha_groups(int per_seq);    // unit groups of one sequence (workspace sizing)
-// bf16 matrix-core step (dc_step.hip); e != nullptr fuses scoring and eviction.
+// bf16 matrix-core step (dc_step.hip); e != nullptr fuses scoring and eviction, or
+// with chunked the scoring: the row keys are then at step_keys(a), row stride a.lmax.
 int launch_step(const DecodeArgs& a, const EvictArgs* e, int D, int G, bool feat, bool chunked,
                 void* stream);
+inline const uint64_t* step_keys(const DecodeArgs& a) { return (const uint64_t*)a.ws_r; }
 bool step_fits(int L, int G, int D, bool feat, int nmoves);
 // Ragged caches: the most rows per unit (after the append) the single-launch
 // step serves at two workgroups per CU, or 0 when it serves no unit of this shape.

@@ -71,7 +71,8 @@ struct UnitDims {
 __device__ __forceinline__ UnitDims unit_dims(const LogzArgs& a, int u) {
   UnitDims d;
   // device values clamped to the host's bounds (rows [1, L], budgets [1, B])
-  d.L = a.unit_len ? (a.unit_len[u] < 1 ? 1 : a.unit_len[u] > a.L ? a.L : a.unit_len[u]) : a.L;
+  const int n = a.unit_len ? a.unit_len[u] + a.len_add : a.L;
+  d.L = n < 1 ? 1 : n > a.L ? a.L : n;
   d.B = a.budgets ? (a.budgets[u] < 1 ? 1 : a.budgets[u] > a.B ? a.B : a.budgets[u]) : a.B;
   d.nk = d.B < d.L ? d.B : d.L;
   return d;

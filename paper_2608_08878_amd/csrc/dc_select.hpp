@@ -29,7 +29,7 @@ __device__ __forceinline__ uint64_t row_key(float s, int32_t pos) {
 // value cannot take an access out of the buffers.
 __device__ __forceinline__ int unit_rows(const EvictArgs& a, int u) {
   if (!a.unit_len) return a.L;
-  const int n = a.unit_len[u];
+  const int n = a.unit_len[u] + a.len_add;
   return n < 1 ? 1 : n > a.L ? a.L : n;
 }
 __device__ __forceinline__ int unit_budget(const EvictArgs& a, int u) {

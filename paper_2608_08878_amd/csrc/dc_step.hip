@@ -481,13 +481,27 @@ __device__ __forceinline__ float new_row_vnorm(const DecodeArgs& a, int u, float
   return *slot;
 }
 
-// Feature update of one row from its weights; returns the updated state.
+// Feature state of one row.
+struct RowState {
+  float al, vn;
+  double nu, de;
+  int32_t p;
+};
+__device__ __forceinline__ void load_row_state(const DecodeArgs& a, size_t gi, RowState& x) {
+  x.al = a.alpha[gi];
+  x.nu = a.num[gi];
+  x.de = a.den[gi];
+  x.p = a.pos[gi];
+  x.vn = a.vnorm[gi];
+}
+
+// Feature update of one row from its weights: x in, the updated state in x and in
+// memory.
 template <int G>
 __device__ __forceinline__ void update_row(const DecodeArgs& a, size_t gi, bool is_new,
                                            const float (&pj)[G], const float (&invl)[G],
-                                           const float (&H)[G], const float* ret, float newnorm,
-                                           float& alpha, double& num, double& den, int32_t& pos,
-                                           float& vn) {
+                                           const float (&H)[G], float2 ret, float newnorm,
+                                           RowState& x) {
   constexpr float invG = 1.0f / G;
   float w[G];
 #pragma unroll
@@ -495,29 +509,21 @@ __device__ __forceinline__ void update_row(const DecodeArgs& a, size_t gi, bool 
   float cz, cn;
   contrib_from_weights<G>(w, H, cz, cn);
   if (is_new) {
-    alpha = cz * invG;
-    den = (double)cz;
-    num = (double)cn;
-    pos = a.T - 1;
-    vn = newnorm;
-    a.pos[gi] = pos;
-    a.vnorm[gi] = vn;
+    x = {cz * invG, newnorm, (double)cn, (double)cz, a.T - 1};
+    a.pos[gi] = x.p;
+    a.vnorm[gi] = x.vn;
   } else {
-    alpha = (a.arec ? 0.0f : a.alpha[gi]) + cz * invG;
-    double z = a.den[gi] + (double)cz;
-    double n = a.num[gi] + (double)cn;
-    pos = a.pos[gi];
-    if (a.retire && pos <= a.pmax_ret) {
-      z = z - (double)ret[0];
-      n = n - (double)ret[1];
+    x.al = (a.arec ? 0.0f : x.al) + cz * invG;
+    x.de = x.de + (double)cz;
+    x.nu = x.nu + (double)cn;
+    if (a.retire && x.p <= a.pmax_ret) {
+      x.de = x.de - (double)ret.x;
+      x.nu = x.nu - (double)ret.y;
     }
-    den = z;
-    num = n;
-    vn = a.vnorm[gi];
   }
-  a.alpha[gi] = alpha;
-  a.den[gi] = den;
-  a.num[gi] = num;
+  a.alpha[gi] = x.al;
+  a.den[gi] = x.de;
+  a.num[gi] = x.nu;
   if (a.sigma) a.sigma[gi] = head_variance<G>(w);
 }
 
@@ -636,21 +642,11 @@ __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArg
   // first group's is requested before the outputs are combined
   const int ngrp = (L + 63) / 64;
   const int ngw = wave < ngrp ? (ngrp - 1 - wave) / SNW + 1 : 0;
-  struct Row {
-    float al, vn;
-    double nu, de;
-    int32_t p;
-  };
-  auto load_row = [&](int k, Row& x) {
+  auto load_row = [&](int k, RowState& x) {
     const int r = 64 * (wave + SNW * k) + lane;
-    const size_t gi = ub + (r < L ? r : L - 1);
-    x.al = a.alpha[gi];
-    x.nu = a.num[gi];
-    x.de = a.den[gi];
-    x.p = a.pos[gi];
-    x.vn = a.vnorm[gi];
+    load_row_state(a, ub + (r < L ? r : L - 1), x);
   };
-  Row cur = {};
+  RowState cur = {};
   {
     float o[G][8];
     if constexpr (!EARLY) pass_b_first<D>(a, u, 0, L, vb);
@@ -697,7 +693,7 @@ __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArg
     // group (one wave) guards its stores.
     const bool part = ngw > 0 && wave + SNW * (ngw - 1) == ngrp - 1 && (L & 63) != 0;
     const int nfull = ngw - (part ? 1 : 0);
-    auto update = [&](int k, const Row& x, bool guard) {
+    auto update = [&](int k, const RowState& x, bool guard) {
       const int r = 64 * (wave + SNW * k) + lane;
       const bool valid = r < L;
       const int ic = valid ? r : L - 1;
@@ -751,7 +747,7 @@ __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArg
       }
     };
     if (ngw > 0) {
-      Row nxt;
+      RowState nxt;
       if constexpr (!EARLY) load_row(0, cur);
       for (int k = 0; k < nfull; ++k) {
         load_row(k + 1 < ngw ? k + 1 : k, nxt);
@@ -807,17 +803,6 @@ __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArg
 // ---------------------------------------------------------------- chunked path
 // ws_part per (unit, chunk): [G] chunk max m_c, [G] l_c, [G] u_c, [G*D] o_c, the
 // sums taken relative to the chunk's own maximum (stepc_d rescales them).
-template <int G>
-__device__ __forceinline__ void chunk_max(const DecodeArgs& a, int u, int D, float (&M)[G]) {
-  const float* parts = a.ws_part + (size_t)u * a.nchunks * (3 * G + G * D);
-#pragma unroll
-  for (int j = 0; j < G; ++j) {
-    float m = parts[j];
-    for (int c = 1; c < a.nchunks; ++c) m = fmaxf(m, parts[(size_t)c * (3 * G + G * D) + j]);
-    M[j] = m;
-  }
-}
-
 // Passes A, P and B of one chunk in one workgroup: K streamed once (logits and
 // retired pairs to the workspace), p = exp(s - m_c) against the chunk maximum,
 // then V streamed once.  The chunk's logits come back from the workspace
@@ -888,51 +873,115 @@ __global__ void __launch_bounds__(SNT) stepc_ab_kernel(DecodeArgs a) {
   }
 }
 
-template <int D, int G, bool FEAT>
-__global__ void __launch_bounds__(SNT) stepc_d_kernel(DecodeArgs a) {
+// SCORE: the one-hidden-layer policy and the ranking key of every row are formed
+// where its features are, so the selection that follows needs no scoring pass over
+// the state (28 B a row).  A row's key takes the place of its retired pair, which
+// only this thread reads (8 B a row at row stride lmax).  Rows are requested before
+// the chunks' sums are combined, one thread per head combines (not every thread
+// all heads), and a thread's rows share the policy's weights.  Measured per step
+// (decode, scores, selection), with a scoring pass of its own -> here: 8 units of
+// 4097 rows 46.7 -> 30.1 us, of 12001 60.1 -> 42.6, 64 of 4097 67.8 -> 54.5; this
+// kernel and the scoring pass on 1024 units of 16385 rows 395 -> 299 us.
+template <int D, int G, bool FEAT, bool SCORE>
+__global__ void __launch_bounds__(SNT) stepc_d_kernel(DecodeArgs a, EvictArgs e) {
+  static_assert(FEAT || !SCORE, "scores need the features");
   __shared__ float newnorm_slot;
+  __shared__ float comb[3][G];          // M, 1 / l, H
   const int c = blockIdx.x, u = a.y0 + blockIdx.y, tid = threadIdx.x;
   const int Lu = len_old_of(a, u) + a.append;
   if (Lu <= a.fused_rows) return;                   // served by the single-launch kernel
   const int r0 = c * a.chunk, r1 = min(Lu, r0 + a.chunk);
   const int PART = 3 * G + G * D;
   const float* parts = a.ws_part + (size_t)u * a.nchunks * PART;
-  float M[G], ls[G], us[G], invl[G], H[G];
-  chunk_max<G>(a, u, D, M);
+  const int newrow = a.append ? len_old_of(a, u) : -1;
+  const size_t ub = (size_t)u * a.cap;
+  const float* s_src = FEAT ? a.ws_s + (size_t)u * a.lmax * G : nullptr;
+  float* r_src = FEAT ? a.ws_r + (size_t)u * a.lmax * 2 : nullptr;
+  // this thread's rows r0 + tid + k SNT, all requested before the chunks' sums
+  // are combined (rows past r1 re-read the last one, unused)
+  constexpr int RB = SCHUNK / SNT;
+  RowState x[RB];
+  float sj[RB][G];
+  float2 ret[RB] = {};
+  if (FEAT && r0 < r1) {
+#pragma unroll
+    for (int k = 0; k < RB; ++k) {
+      const int i = r0 + tid + k * SNT, ic = i < r1 ? i : r1 - 1;
+      load_row_state(a, ub + ic, x[k]);
+      if constexpr (G >= 4) {
+#pragma unroll
+        for (int j = 0; j < G; j += 4) {
+          const f32x4_t v = *reinterpret_cast<const f32x4_t*>(s_src + (size_t)ic * G + j);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sj[k][j + r] = v[r];
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < G; ++j) sj[k][j] = s_src[(size_t)ic * G + j];
+      }
+      if (a.retire) ret[k] = *reinterpret_cast<const float2*>(r_src + 2 * (size_t)ic);
+    }
+  }
   // chunk c's sums move to the common maximum M: with f = e^(m_c - M),
-  // l += f l_c, u += f (u_c + (m_c - M) l_c), o += f o_c (a neutral chunk: f = 0)
+  // l += f l_c, u += f (u_c + (m_c - M) l_c), o += f o_c (a neutral chunk: f = 0);
+  // one thread per head, the chunks in order
+  if (tid < G) {
+    float m = parts[tid];
+#pragma unroll 4
+    for (int cc = 1; cc < a.nchunks; ++cc) m = fmaxf(m, parts[(size_t)cc * PART + tid]);
+    float l = 0.0f, uu = 0.0f;
+#pragma unroll 4
+    for (int cc = 0; cc < a.nchunks; ++cc) {
+      const float* pc = parts + (size_t)cc * PART + tid;
+      const float dm = pc[0] - m;
+      const float f = __builtin_amdgcn_exp2f(dm * LOG2E);
+      l = l + f * pc[G];
+      uu = uu + f * (pc[2 * G] + dm * pc[G]);
+    }
+    const float il = 1.0f / l;
+    comb[0][tid] = m;
+    comb[1][tid] = il;
+    comb[2][tid] = __logf(l) - uu * il;
+  }
+  const float newnorm = FEAT && a.append && newrow >= r0 && newrow < r1
+                            ? new_row_vnorm<D>(a, u, &newnorm_slot) : 0.0f;
+  __syncthreads();
+  float M[G], invl[G], H[G];
 #pragma unroll
   for (int j = 0; j < G; ++j) {
-    float l = 0.0f, uu = 0.0f;
-    for (int cc = 0; cc < a.nchunks; ++cc) {
-      const float* pc = parts + (size_t)cc * PART;
-      const float dm = pc[j] - M[j];
-      const float f = __builtin_amdgcn_exp2f(dm * LOG2E);
-      l = l + f * pc[G + j];
-      uu = uu + f * (pc[2 * G + j] + dm * pc[G + j]);
-    }
-    ls[j] = l;
-    us[j] = uu;
-    invl[j] = 1.0f / l;
-    H[j] = __logf(l) - uu * invl[j];
+    M[j] = comb[0][j];
+    invl[j] = comb[1][j];
+    H[j] = comb[2][j];
   }
   if constexpr (FEAT) {
-    const int newrow = a.append ? len_old_of(a, u) : -1;
-    const float newnorm = (a.append && newrow >= r0 && newrow < r1)
-                              ? new_row_vnorm<D>(a, u, &newnorm_slot) : 0.0f;
-    const float* s_src = a.ws_s + (size_t)u * a.lmax * G;
-    const float* r_src = a.ws_r + (size_t)u * a.lmax * 2;
-    const size_t ub = (size_t)u * a.cap;
-    for (int i = r0 + tid; i < r1; i += SNT) {
+#pragma unroll
+    for (int k = 0; k < RB; ++k) {
+      const int i = r0 + tid + k * SNT;
+      if (i >= r1) continue;
       float pj[G];
 #pragma unroll
-      for (int j = 0; j < G; ++j)
-        pj[j] = __builtin_amdgcn_exp2f((s_src[(size_t)i * G + j] - M[j]) * LOG2E);
-      float al, vn;
-      double nu, de;
-      int32_t ps;
-      update_row<G>(a, ub + i, i == newrow, pj, invl, H, r_src + 2 * (size_t)i, newnorm, al, nu,
-                    de, ps, vn);
+      for (int j = 0; j < G; ++j) pj[j] = __builtin_amdgcn_exp2f((sj[k][j] - M[j]) * LOG2E);
+      update_row<G>(a, ub + i, i == newrow, pj, invl, H, ret[k], newnorm, x[k]);
+    }
+    if constexpr (SCORE) {
+      // (a unit that keeps every row needs no key; past the last row of a chunk
+      // the state is that of its last row)
+      if (r0 < r1 && (e.scores_out || unit_budget(e, u) < Lu)) {
+        const float invT = 1.0f / (float)a.T;
+        float f[RB][4], sc[RB];
+#pragma unroll
+        for (int k = 0; k < RB; ++k) make_features(x[k].al, x[k].vn, x[k].nu, x[k].de, x[k].p, invT, f[k]);
+        const int rows = (r1 - r0 + SNT - 1) / SNT;
+        policy_scores<RB>(e, f, sc, rows);
+#pragma unroll
+        for (int k = 0; k < RB; ++k) {
+          const int i = r0 + tid + k * SNT;
+          if (i >= r1) continue;
+          if (e.scores_out) e.scores_out[(size_t)u * e.L + i] = sc[k];
+          reinterpret_cast<uint64_t*>(r_src)[i] =
+              row_key(e.sample ? sampled_score(e, sc[k], x[k].p, u) : sc[k], x[k].p);
+        }
+      }
     }
   }
   if (c != 0) return;
@@ -960,12 +1009,13 @@ __global__ void unit_len_add_kernel(int32_t* len, int units, int add) {
   if (u < units) len[u] += add;
 }
 
-__global__ void unit_len_min_kernel(int32_t* len, const int32_t* budgets, int b, int units) {
+__global__ void unit_len_min_kernel(int32_t* len, const int32_t* budgets, int b, int add, int units) {
   const int u = blockIdx.x * 256 + threadIdx.x;
   if (u < units) {
     int bu = budgets ? budgets[u] : b;
     bu = bu < 1 ? 1 : bu > b ? b : bu;            // the clamp the selection applies
-    len[u] = bu < len[u] ? bu : len[u];
+    const int n = len[u] + add;
+    len[u] = bu < n ? bu : n;
   }
 }
 
@@ -975,9 +1025,9 @@ int launch_unit_len_add(int32_t* len, int units, int add, void* stream) {
   return (int)hipGetLastError();
 }
 
-int launch_unit_len_min(int32_t* len, const int32_t* budgets, int b, int units, void* stream) {
+int launch_unit_len_min(int32_t* len, const int32_t* budgets, int b, int add, int units, void* stream) {
   hipLaunchKernelGGL(unit_len_min_kernel, dim3((units + 255) / 256), dim3(256), 0,
-                     (hipStream_t)stream, len, budgets, b, units);
+                     (hipStream_t)stream, len, budgets, b, add, units);
   return (int)hipGetLastError();
 }
 
@@ -1055,8 +1105,11 @@ static int launch_step_t(const DecodeArgs& a, const EvictArgs* e, bool feat, boo
     for_grid_y(a.units, [&](int y0, int ny) {
       DecodeArgs b = a;
       b.y0 = y0;
-      if (feat) hipLaunchKernelGGL((stepc_d_kernel<D, G, true>), dim3(a.nchunks, ny), dim3(SNT), 0, s, b);
-      else hipLaunchKernelGGL((stepc_d_kernel<D, G, false>), dim3(a.nchunks, ny), dim3(SNT), 0, s, b);
+      const EvictArgs none = {};
+      const dim3 grid(a.nchunks, ny);
+      if (feat && e) hipLaunchKernelGGL((stepc_d_kernel<D, G, true, true>), grid, dim3(SNT), 0, s, b, *e);
+      else if (feat) hipLaunchKernelGGL((stepc_d_kernel<D, G, true, false>), grid, dim3(SNT), 0, s, b, none);
+      else hipLaunchKernelGGL((stepc_d_kernel<D, G, false, false>), grid, dim3(SNT), 0, s, b, none);
     });
   }
   return (int)hipGetLastError();
