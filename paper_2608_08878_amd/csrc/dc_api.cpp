@@ -37,42 +37,9 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Units below which one workgroup per unit leaves most of the chip idle.
 constexpr int FEW_UNITS = 128;
-// bf16 caches of more than one chunk of rows on this many units or fewer take
-// the chunked decode as well.  Measured per step (decode, scoring, selection
-// and compaction), single launch -> chunked: 8 units 43.5 -> 39.0 us at 2049
-// rows and 59.6 -> 42.3 us at 3073 rows, 48 units 45.9 -> 42.1 and
-// 61.5 -> 55.6 us; at 64 units 2049 rows favour the single launch (45.7
-// against 51.9 us), and 1025 rows always do (28 us against 33-36 us).
-constexpr int VERY_FEW_UNITS = 48;
-constexpr int MIN_CHUNK = 512;   // rows per workgroup on the chunked path, at least
-
-// Rows per workgroup on the chunked path.  Many units (or fp32): full chunks.
-// Few bf16 units: at most 16 chunks per unit (every workgroup of the combining
-// kernels walks all of its unit's partials) and about 512 workgroups in all,
-// rounded up to 128 rows and kept within [512, full chunk].  Measured for 1-64
-// units at 4097-32769 rows: 1-8 units of 4097 rows take 46-47 us per step
-// against 61-63 us with full chunks; the rule never measured slower.
-int chunk_rows(const dc_dims* d, int L) {
-  const int c = dc::decode_chunk_rows();
-  const long U = (long)units_of(d);
-  if (d->dtype != DC_BF16 || U >= FEW_UNITS) return c;
-  const long by_chunks = (L + 15) / 16, by_groups = ((long)L * U + 511) / 512;
-  const long want = by_chunks > by_groups ? by_chunks : by_groups;
-  const long r = (want + 127) / 128 * 128;
-  return r < MIN_CHUNK ? MIN_CHUNK : r > c ? c : (int)r;
-}
-
-int nchunks_of(const dc_dims* d, int L) {
-  const int c = chunk_rows(d, L);
-  return (L + c - 1) / c;
-}
-
-// Chunks of any length up to L: the workspace bound (the chunk grows with L,
-// so the count is not monotone in L).
-int nchunks_bound(const dc_dims* d, int L) {
-  const bool few = d->dtype == DC_BF16 && units_of(d) < FEW_UNITS;
-  return few ? (L + MIN_CHUNK - 1) / MIN_CHUNK : nchunks_of(d, L);
-}
+constexpr int CUS = 256;
+constexpr int MIN_CHUNK = 256;   // rows per workgroup on the chunked path, at least
+constexpr int WS_CHUNK = 512;    // rows per chunk of few units that the workspace is sized for
 
 // Per-unit row stride of the decode scratch: L rows plus padding that takes the
 // stores of lanes past the last row (so those stores need no branch), rounded
@@ -80,12 +47,55 @@ int nchunks_bound(const dc_dims* d, int L) {
 // tile of retired pairs is then exactly one 128-byte line).
 int scratch_rows(int L) { return (L + 8 + 31) / 32 * 32; }
 
+// Floats of one chunk's softmax partials.
+int part_floats(const dc_dims* d) { return 3 * group_of(d) + group_of(d) * d->head_dim; }
+
+// Chunks of any length up to L for which the workspace is sized.
+int nchunks_bound(const dc_dims* d, int L) {
+  const int c = d->dtype == DC_BF16 && units_of(d) < FEW_UNITS ? WS_CHUNK : dc::decode_chunk_rows();
+  return (L + c - 1) / c;
+}
+
 // Scratch of the chunked decode path for caches of L rows.
 size_t split_bytes(const dc_dims* d, int L) {
-  const size_t U = (size_t)units_of(d), G = group_of(d), D = d->head_dim;
+  const size_t U = (size_t)units_of(d), G = group_of(d);
   const size_t rows = U * (size_t)scratch_rows(L) * (G + 3) * sizeof(float);
-  const size_t parts = U * (size_t)nchunks_bound(d, L) * (3 * G + G * D) * sizeof(float);
+  const size_t parts = U * (size_t)nchunks_bound(d, L) * part_floats(d) * sizeof(float);
   return align256(rows) + align256(parts);
+}
+
+// Rows per workgroup on the chunked path.  Many units (or fp32): full chunks.  Few
+// bf16 units: a CU streams one or two chunks no faster than the misses it can have
+// in flight allow, so the chunk is the one (a multiple of 128 rows: two tiles per
+// wave at 256) whose fullest CU has the fewest rows to stream, a chunk costing
+// about 160 rows of its own and 56 in the combination; at most 16 chunks, and no
+// more than the workspace has room for.  Measured per step, against about 512 workgroups of 512
+// rows or more: 64 units of 4097 rows 54.2 -> 50.0 us, 32 45.2 -> 37.1, 48 47.2 -> 42.9, of
+// 3073 45.0 -> 37.6, 8 of 1025 27.0 -> 23.9.
+int chunk_rows(const dc_dims* d, int L) {
+  const int full = dc::decode_chunk_rows();
+  const long U = (long)units_of(d);
+  if (d->dtype != DC_BF16 || U >= FEW_UNITS) return full;
+  const size_t rows = (size_t)U * scratch_rows(L), G = group_of(d);
+  const size_t room = split_bytes(d, L) - align256(rows * (G + 2) * sizeof(float));
+  const long most = (long)(room / ((size_t)U * part_floats(d) * sizeof(float)));
+  int best = full;
+  long least = 0;
+  for (int c = full; c >= MIN_CHUNK; c -= 128) {
+    const long n = (L + c - 1) / c;
+    if (c < full && (n > 16 || n > most)) break;
+    const long cost = ((U * n + CUS - 1) / CUS) * (c + 160) + 56 * n;
+    if (c == full || cost < least) {
+      least = cost;
+      best = c;
+    }
+  }
+  return best;
+}
+
+int nchunks_of(const dc_dims* d, int L) {
+  const int c = chunk_rows(d, L);
+  return (L + c - 1) / c;
 }
 
 bool use_split(const dc_dims* d, int L, bool feat) {
@@ -93,6 +103,19 @@ bool use_split(const dc_dims* d, int L, bool feat) {
   if (feat && !dc::decode_fits_lds(L, G, d->head_dim)) return true;
   // few units: spread one unit's rows over several workgroups
   return units_of(d) < FEW_UNITS && L > 2 * dc::decode_chunk_rows();
+}
+
+// bf16 feature steps on few units that take the chunked kernels though one launch
+// would hold the cache, whose one CU per unit is then what it waits for.  Measured
+// per step (decode, scores, selection), one launch -> chunked: 8 units of 897 rows
+// 24.4 -> 25.8 us, of 1025 27.4 -> 23.9, of 1537 35.2 -> 26.9, 48 of 1025 28.2 -> 25.3; 64
+// of 1025 27.9 -> 28.3, of 1281 33.3 -> 30.4, of 3073 62.0 -> 43.4; 96 of 1537 37.8 -> 39.1, of
+// 2049 46.0 -> 44.7; 120 of 2049 46.2 -> 46.8, of 3073 63.2 -> 58.5.  Rows of 64 elements
+// take twice as many (8 units of 1025: 18.0 -> 19.6).
+bool few_split(const dc_dims* d, int L) {
+  const long U = (long)units_of(d), w = (long)L * d->head_dim;
+  if (U >= FEW_UNITS) return false;
+  return w > 128L * (U <= 48 ? 1000 : U <= 64 ? 1152 : U <= 96 ? 1792 : 2304);
 }
 
 size_t evict_bytes(const dc_dims* d, int L) { return align256(dc::evict_ws_bytes((int)units_of(d), L)); }
@@ -234,7 +257,9 @@ dc_status prep_decode(const dc_dims* dims, const dc_kv* kv, const dc_feat* feat,
   if (dims->dtype == DC_BF16)
     split = ragged || !dc::step_fits(L, G, D, feat != nullptr, 0) ||
             (U < FEW_UNITS && L > 2 * dc::step_chunk_rows()) ||
-            (U <= VERY_FEW_UNITS && L > dc::step_chunk_rows());
+            (U <= 48 && L > dc::step_chunk_rows()) ||
+            // (a workspace that holds only the single launch's scratch takes that)
+            (feat && few_split(dims, L) && ws && ws_bytes >= split_bytes(dims, L));
   else
     split = use_split(dims, L, feat != nullptr);
   // the matrix-core unit path parks each row's retired (cz, cn) in the workspace
@@ -285,10 +310,13 @@ dc_status prep_decode(const dc_dims* dims, const dc_kv* kv, const dc_feat* feat,
     a.lmax = scratch_rows(L);
     a.chunk = chunk_rows(dims, L);
     a.nchunks = nchunks_of(dims, L);
+    a.comb64 = U < FEW_UNITS;
     a.ws_s = base;
     a.ws_r = base + rows * G;
     a.ws_v = base + rows * (G + 2);
-    a.ws_part = (float*)((char*)ws + align256(rows * (G + 3) * sizeof(float)));
+    // (bf16: no value norms, the partials start in their place)
+    const int per_row = dims->dtype == DC_BF16 ? G + 2 : G + 3;
+    a.ws_part = (float*)((char*)ws + align256(rows * per_row * sizeof(float)));
   }
   return DC_OK;
 }

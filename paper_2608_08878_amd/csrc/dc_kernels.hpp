@@ -45,6 +45,7 @@ struct DecodeArgs {
                         // past L are padding that absorbs the stores of lanes without a row)
   int chunk;
   int nchunks;
+  int comb64;           // combine the chunks' sums in binary64 (few units, short chunks)
   int fused_rows;       // ragged caches: units of at most this many rows after the append were
                         // served by the single-launch kernel; the chunked kernels skip them (0: none)
 };

@@ -929,19 +929,37 @@ __global__ void __launch_bounds__(SNT) stepc_d_kernel(DecodeArgs a, EvictArgs e)
     float m = parts[tid];
 #pragma unroll 4
     for (int cc = 1; cc < a.nchunks; ++cc) m = fmaxf(m, parts[(size_t)cc * PART + tid]);
-    float l = 0.0f, uu = 0.0f;
+    float il, h;
+    if (a.comb64) {
+      // short chunks: where one row takes nearly all the weight, l is 1 plus little
+      // and the entropy lives in the little, which many float32 additions would eat
+      double l = 0.0, uu = 0.0;
 #pragma unroll 4
-    for (int cc = 0; cc < a.nchunks; ++cc) {
-      const float* pc = parts + (size_t)cc * PART + tid;
-      const float dm = pc[0] - m;
-      const float f = __builtin_amdgcn_exp2f(dm * LOG2E);
-      l = l + f * pc[G];
-      uu = uu + f * (pc[2 * G] + dm * pc[G]);
+      for (int cc = 0; cc < a.nchunks; ++cc) {
+        const float* pc = parts + (size_t)cc * PART + tid;
+        const float dm = pc[0] - m;
+        const double f = (double)__builtin_amdgcn_exp2f(dm * LOG2E);
+        l += f * (double)pc[G];
+        uu += f * ((double)pc[2 * G] + (double)dm * (double)pc[G]);
+      }
+      il = (float)(1.0 / l);
+      h = (float)(log(l) - uu / l);
+    } else {
+      float l = 0.0f, uu = 0.0f;
+#pragma unroll 4
+      for (int cc = 0; cc < a.nchunks; ++cc) {
+        const float* pc = parts + (size_t)cc * PART + tid;
+        const float dm = pc[0] - m;
+        const float f = __builtin_amdgcn_exp2f(dm * LOG2E);
+        l = l + f * pc[G];
+        uu = uu + f * (pc[2 * G] + dm * pc[G]);
+      }
+      il = 1.0f / l;
+      h = __logf(l) - uu * il;
     }
-    const float il = 1.0f / l;
     comb[0][tid] = m;
     comb[1][tid] = il;
-    comb[2][tid] = __logf(l) - uu * il;
+    comb[2][tid] = h;
   }
   const float newnorm = FEAT && a.append && newrow >= r0 && newrow < r1
                             ? new_row_vnorm<D>(a, u, &newnorm_slot) : 0.0f;

@@ -758,3 +758,42 @@ def test_early_requests_keep_the_bits(D, G):
     for i, (a, b) in enumerate(zip(*got)):
         a = a[:, :16] if i == 0 else a[:16]
         assert torch.equal(a, b), i
+
+
+@pytest.mark.parametrize("D,G,U,n,budget", [(128, 4, 3, 1000, 1000), (128, 4, 3, 1599, 1200), (64, 4, 5, 2040, 2040),
+                                            (128, 8, 5, 1024, 1024), (128, 1, 4, 1300, 1299), (64, 2, 7, 2030, 100),
+                                            (128, 4, 64, 1280, 1280), (128, 4, 90, 1800, 1800),
+                                            (128, 4, 100, 2310, 2310)])
+def test_few_units_chunked_agrees_with_the_single_launch(D, G, U, n, budget):
+    """Few units of short caches take the chunked kernels when the workspace holds their scratch,
+    the single launch when it holds only that one's: same attention, features and scores up to
+    float32 rounding, in the slots that each selection's own scores give."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    k, v, q, kn, vn = rnd(U, n + 2, D), rnd(U, n + 2, D), rnd(2, U, G, D), rnd(2, U, D), rnd(2, U, D)
+    params = torch.randn(32 * 4 + 32 + 32 + 1, generator=gen, device="cuda") * 0.1
+    got = []
+    for small in (False, True):
+        buf = DecodeBuffers(U, 1, G, 1, D, n + 2, "bf16", 1)
+        buf.k.copy_(k)
+        buf.v.copy_(v)
+        buf.feat_init(n, 0)
+        if small:
+            buf.ws_bytes = U * ((n + 2 + 8 + 31) // 32 * 32) * 8 + 256
+        out, scores = torch.empty_like(q), torch.full((U, n + 2), float("nan"), device="cuda")
+        kept = torch.empty((U, budget), dtype=torch.int32, device="cuda")
+        print(f"few units D={D} G={G} U={U} n={n} small={small}", flush=True)
+        buf.decode_step(q[0], kn[0], vn[0], out[0])
+        pre = [x.clone() for x in (buf.alpha, buf.num, buf.den, buf.pos, buf.vnorm)]
+        buf.decode_evict(make_policy(params, (32,)), budget, q[1], kn[1], vn[1], out[1], scores, kept)
+        torch.cuda.synchronize()
+        for u in {0, U - 1}:
+            keep = osel.top_budget(scores[u].double().cpu().numpy(), np.arange(n + 2), budget)
+            assert set(kept[u].cpu().numpy().tolist()) == set(np.asarray(keep).tolist()), u
+        got.append((out.float(), scores, [x[:, :n + 1].double() for x in pre]))
+    (o0, s0, p0), (o1, s1, p1) = got
+    assert (o0 - o1).abs().max() <= 2 * 2.0 ** -8 * o1.abs().max()           # one bfloat16 rounding each
+    # float32 sums of n weights in another order, and exp2 of logits a rounding apart
+    for a, b in zip(p0, p1):
+        assert (a - b).abs().max() <= (n + 64) * 2.0 ** -23 * b.abs().max() / 8, (a - b).abs().max()
+    assert (s0 - s1).abs().max() <= (n + 64) * 2.0 ** -23 / 8 * (1 + s1.abs().max())
