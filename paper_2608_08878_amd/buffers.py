@@ -13,8 +13,10 @@ DC_DTYPE = {"f32": B.DC_F32, "bf16": B.DC_BF16}
 
 
 def stream_handle(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        # the raw handle: building a Stream object costs 2.8 us of a small call
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    return ctypes.c_void_p(stream.cuda_stream)
 
 
 class DecodeBuffers:

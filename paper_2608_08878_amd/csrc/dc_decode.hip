@@ -532,11 +532,11 @@ static int launch_t(const DecodeArgs& a, bool feat, bool split, hipStream_t s) {
     size_t lds = decode_lds_bytes(a.L, G, D, feat);
     if (feat) {
       auto k = decode_unit_kernel<DTYPE, D, G, true>;
-      hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      allow_lds((const void*)k, lds);
       hipLaunchKernelGGL(k, dim3(a.units), dim3(NTH), lds, s, a);
     } else {
       auto k = decode_unit_kernel<DTYPE, D, G, false>;
-      hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      allow_lds((const void*)k, lds);
       hipLaunchKernelGGL(k, dim3(a.units), dim3(NTH), lds, s, a);
     }
   } else {

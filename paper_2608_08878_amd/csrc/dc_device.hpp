@@ -12,6 +12,12 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr float LOG2E = 1.44269504088896340736f;
 constexpr float NEG_BIG = -1.0e30f;   // "minus infinity" that keeps 0 * x finite
 
+// Dynamic LDS beyond the 64 KB a launch has by default (static LDS here stays under
+// 16 KB) has to be allowed; the call is host time on every launch, so small ones skip it.
+inline void allow_lds(const void* kernel, size_t bytes) {
+  if (bytes > 48 * 1024) hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 // Row layout: one lane owns 16 contiguous bytes of a key/value row.
 template <int DTYPE, int D>
 struct RowT {

@@ -155,7 +155,7 @@ static int launch_select_t(const EvictArgs& a, const uint64_t* keys, int kstride
   if (a.evict || a.unit_len || a.budgets) {
     const bool wide = nmv >= 4096;
     auto k = wide ? select_kernel<DTYPE, D, ENT> : select_kernel<DTYPE, D, 512>;
-    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    allow_lds((const void*)k, dyn);
     hipLaunchKernelGGL(k, dim3(a.units), dim3(wide ? ENT : 512), dyn, s, a, keys, kstride);
   } else if (a.kept_out) {
     hipLaunchKernelGGL(identity_kept_kernel, dim3(1024), dim3(256), 0, s, a.kept_out, a.units, a.L);
@@ -177,7 +177,7 @@ static int launch_evict_t(const EvictArgs& a, uint64_t* ws_keys, hipStream_t s) 
     // the one-hidden-layer policy on a short cache: scores in registers
     const bool half = a.L <= 512 * 9;
     auto k = half ? score_select_kernel<DTYPE, D, 512, 9> : score_select_kernel<DTYPE, D, ENT, REG_KPT>;
-    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    allow_lds((const void*)k, dyn);
     hipLaunchKernelGGL(k, dim3(a.units), dim3(half ? 512 : ENT), dyn, s, b);
     return (int)hipGetLastError();
   }

@@ -1086,7 +1086,7 @@ static int launch_step_t(const DecodeArgs& a, const EvictArgs* e, bool feat, boo
     ee.mv_ints = move_list_ints(nm);
     const size_t lds = step_lds_bytes(a.L, G, D, feat, nm);
     auto pick = [&](auto kern) {
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      allow_lds((const void*)kern, lds);
       hipLaunchKernelGGL(kern, dim3(a.units), dim3(SNT), lds, s, a, ee);
     };
     // (the fused evicting variants serve the one-hidden-layer four-input policy)
