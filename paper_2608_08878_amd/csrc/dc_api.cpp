@@ -667,15 +667,23 @@ dc_status dc_decode_evict_units(const dc_dims* dims, dc_kv* kv, dc_feat* feat,
     af.L = a.L < Lf ? a.L : Lf;     // the rows one workgroup serves (LDS); longer units leave
     dc::EvictArgs ef = e;
     ef.L = a.L;                     // row stride of scores_out
-    if (dc::launch_step(af, &ef, D, G, true, false, hip_stream) != 0) return DC_ERR_HIP;
     if (a.L > af.L) {
       // the longer units: chunked decode with their scores, then their selection
       dc::DecodeArgs ac = a;
       ac.fused_rows = af.L;
       dc::EvictArgs el = e;
       el.fused_rows = af.L;
-      st = decode_then_evict(dims, kv, ac, el, true, hip_stream);
-      if (st != DC_OK) return st;
+      if (G == 4) {
+        if (dc::launch_step_mixed(af, ef, ac, el, D, G, hip_stream) != 0) return DC_ERR_HIP;
+        el.len_add = a.append;
+        if (dc::launch_select_keys(el, dc::step_keys(ac), ac.lmax, D, hip_stream) != 0) return DC_ERR_HIP;
+      } else {
+        if (dc::launch_step(af, &ef, D, G, true, false, hip_stream) != 0) return DC_ERR_HIP;
+        st = decode_then_evict(dims, kv, ac, el, true, hip_stream);
+        if (st != DC_OK) return st;
+      }
+    } else if (dc::launch_step(af, &ef, D, G, true, false, hip_stream) != 0) {
+      return DC_ERR_HIP;
     }
     e.len_add = a.append;             // every kernel has read the old lengths
   }

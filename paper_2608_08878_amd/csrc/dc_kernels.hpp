@@ -183,6 +183,10 @@ int global_alpha_groups(int per_seq);    // unit groups of one sequence (workspa
 // with chunked the scoring: the row keys are then at step_keys(a), row stride a.lmax.
 int launch_step(const DecodeArgs& a, const EvictArgs* e, int D, int G, bool feat, bool chunked,
                 void* stream);
+// A ragged step with per-unit budgets: the units that fit on chip (a, e) and the
+// longer units' chunks (ac) in one launch, then the latter's features and keys (el).
+int launch_step_mixed(const DecodeArgs& a, const EvictArgs& e, const DecodeArgs& ac, const EvictArgs& el,
+                      int D, int G, void* stream);
 inline const uint64_t* step_keys(const DecodeArgs& a) { return (const uint64_t*)a.ws_r; }
 bool step_fits(int L, int G, int D, bool feat, int nmoves);
 // Ragged caches: the most rows per unit (after the append) the single-launch

@@ -591,18 +591,18 @@ struct RowStride {
 // waits, and on long rows, it costs instead: 512 of 1025 60.0 -> 60.7 us, 4096 of
 // 4097 1701 -> 1712.  The bits are the same.
 template <int D, int G, bool FEAT, bool EVICT, bool SIG, bool SMP, bool RAG, bool EARLY>
-__global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArgs a, EvictArgs e) {
+__device__ __forceinline__ void step_unit_body(const DecodeArgs& a, const EvictArgs& e, const int u,
+                                               float* lds) {
   static_assert(!SIG || (FEAT && !EVICT), "sigma is stored by the decode-only variant");
   static_assert(!SMP || (EVICT && RowStride<G>::RS >= 4), "sampling keeps the score beside the key");
   static_assert(!RAG || (FEAT && EVICT && !SIG && !SMP && RowStride<G>::RS >= 4),
                 "the ragged variant plans its moves beside the keys");
   constexpr int LPR = MG<D>::LPR;
   constexpr int RS = RowStride<G>::RS, KS = RowStride<G>::KS;
-  extern __shared__ float lds[];
   __shared__ SelShared sh;
   __shared__ float stat[SNW * 2 * G + 2 * G];
   __shared__ float newnorm_slot;
-  const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int L = RAG ? len_old_of(a, u) + a.append : a.L;
   if constexpr (RAG) {
     if (L > a.L || L < 1) return;                     // whole workgroup: the chunked kernels' unit
@@ -800,6 +800,12 @@ __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArg
   }
 }
 
+template <int D, int G, bool FEAT, bool EVICT, bool SIG, bool SMP, bool RAG, bool EARLY>
+__global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArgs a, EvictArgs e) {
+  extern __shared__ float lds[];
+  step_unit_body<D, G, FEAT, EVICT, SIG, SMP, RAG, EARLY>(a, e, blockIdx.x, lds);
+}
+
 // ---------------------------------------------------------------- chunked path
 // ws_part per (unit, chunk): [G] chunk max m_c, [G] l_c, [G] u_c, [G*D] o_c, the
 // sums taken relative to the chunk's own maximum (stepc_d rescales them).
@@ -809,13 +815,19 @@ __global__ void __launch_bounds__(SNT, G > 4 ? 2 : 4) step_unit_kernel(DecodeArg
 // while still in L2 (this workgroup stored them moments before).  RET: the
 // step retires a step leaving the window; without one no retired pair is
 // stored (the feature pass reads them only when the step retires).
+template <int D, int G>
+struct ChunkLds {                         // floats of LDS of one chunk's workgroup
+  float p[SCHUNK * G], o[SNW * G * D], stat[SNW * 2 * G + 2 * G];
+};
+
 template <int D, int G, bool FEAT, bool RET>
-__global__ void __launch_bounds__(SNT) stepc_ab_kernel(DecodeArgs a) {
+__device__ __forceinline__ void stepc_ab_body(const DecodeArgs& a, const int c, const int u,
+                                              ChunkLds<D, G>& sm) {
   constexpr int LPR = MG<D>::LPR;
-  __shared__ float pbuf[SCHUNK * G];
-  __shared__ float obuf[SNW * G * D];
-  __shared__ float stat[SNW * 2 * G + 2 * G];
-  const int c = blockIdx.x, u = a.y0 + blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float* pbuf = sm.p;
+  float* obuf = sm.o;
+  float* stat = sm.stat;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int Lu = len_old_of(a, u) + a.append;       // this unit's rows (ragged caches: per unit)
   if (Lu <= a.fused_rows) return;                   // served by the single-launch kernel
   const int r0 = c * a.chunk, r1 = min(Lu, r0 + a.chunk), n = r1 - r0;
@@ -870,6 +882,30 @@ __global__ void __launch_bounds__(SNT) stepc_ab_kernel(DecodeArgs a) {
         part[G + j] = ls[j];
         part[2 * G + j] = us[j];
       }
+  }
+}
+
+template <int D, int G, bool FEAT, bool RET>
+__global__ void __launch_bounds__(SNT) stepc_ab_kernel(DecodeArgs a) {
+  __shared__ ChunkLds<D, G> sm;
+  stepc_ab_body<D, G, FEAT, RET>(a, blockIdx.x, a.y0 + blockIdx.y, sm);
+}
+
+// A ragged step's two decode kernels in one launch: workgroups 0 .. units - 1 take
+// the units that fit on chip (step_unit_body, RAG), the others the longer units'
+// chunks.  The first kind alone leaves half the chip idle in its last round (768
+// units on 512 places), which the chunks fill.  Measured (one launch after the other
+// -> here): 768 units of 4097 rows and 256 of 16385 840 -> 815 us; the step of 96 units
+// of 4001 and 32 of 16001 rows 247 -> 210, of 512 of 501 and 512 of 5001 431 -> 392.
+template <int D, int G, bool RET, bool EARLY>
+__global__ void __launch_bounds__(SNT, 4) step_mixed_kernel(DecodeArgs a, EvictArgs e, DecodeArgs ac) {
+  extern __shared__ float lds[];
+  if ((int)blockIdx.x < a.units) {
+    step_unit_body<D, G, true, true, false, false, true, EARLY>(a, e, blockIdx.x, lds);
+  } else {
+    const int b = blockIdx.x - a.units;
+    stepc_ab_body<D, G, true, RET>(ac, b % ac.nchunks, b / ac.nchunks,
+                                   *reinterpret_cast<ChunkLds<D, G>*>(lds));
   }
 }
 
@@ -1074,6 +1110,12 @@ int step_ragged_rows(int G, int D) {
   return L;
 }
 
+// One workgroup per CU at most (G > 4: its registers allow no second), or more
+// rounds than one of not too long rows (step_unit_body's comment has both sides).
+static bool step_early(const DecodeArgs& a, int G) {
+  return G > 4 || a.units <= 256 || a.L <= 512 || (a.units > 512 && a.L <= 3584);
+}
+
 template <int D, int G>
 static int launch_step_t(const DecodeArgs& a, const EvictArgs* e, bool feat, bool chunked,
                          hipStream_t s) {
@@ -1090,10 +1132,7 @@ static int launch_step_t(const DecodeArgs& a, const EvictArgs* e, bool feat, boo
       hipLaunchKernelGGL(kern, dim3(a.units), dim3(SNT), lds, s, a, ee);
     };
     // (the fused evicting variants serve the one-hidden-layer four-input policy)
-    // one workgroup per CU at most (G > 4: its registers allow no second), or more
-    // rounds than one of not too long rows
-    // (step_unit_kernel's comment has both sides)
-    const bool early = G > 4 || a.units <= 256 || a.L <= 512 || (a.units > 512 && a.L <= 3584);
+    const bool early = step_early(a, G);
 #define DC_STEP(...) do { if (early) pick(step_unit_kernel<D, G, __VA_ARGS__, true>); else pick(step_unit_kernel<D, G, __VA_ARGS__, false>); } while (0)
     if (!feat) DC_STEP(false, false, false, false, false);
     else if (e && e->sample) {
@@ -1131,6 +1170,40 @@ static int launch_step_t(const DecodeArgs& a, const EvictArgs* e, bool feat, boo
     });
   }
   return (int)hipGetLastError();
+}
+
+// The ragged step in one launch for the decode of all units, then the features and
+// scores of the longer ones; hipErrorInvalidValue where the two do not share a CU's
+// LDS and registers (the caller takes two launches).
+template <int D>
+static int launch_step_mixed_t(const DecodeArgs& a, const EvictArgs& e, const DecodeArgs& ac,
+                               const EvictArgs& el, hipStream_t s) {
+  constexpr int G = 4;
+  size_t lds = step_lds_bytes(a.L, G, D, true, 0);
+  lds = lds > sizeof(ChunkLds<D, G>) ? lds : sizeof(ChunkLds<D, G>);
+  const long blocks = (long)a.units * (1 + ac.nchunks);
+  if (lds > (size_t)S_LDS / 2 || blocks > (1l << 30)) return (int)hipErrorInvalidValue;
+  auto pick = [&](auto kern) {
+    allow_lds((const void*)kern, lds);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(SNT), lds, s, a, e, ac);
+  };
+  const bool early = step_early(a, G);
+  if (ac.retire) early ? pick(step_mixed_kernel<D, G, true, true>) : pick(step_mixed_kernel<D, G, true, false>);
+  else early ? pick(step_mixed_kernel<D, G, false, true>) : pick(step_mixed_kernel<D, G, false, false>);
+  for_grid_y(ac.units, [&](int y0, int ny) {
+    DecodeArgs b = ac;
+    b.y0 = y0;
+    hipLaunchKernelGGL((stepc_d_kernel<D, G, true, true>), dim3(ac.nchunks, ny), dim3(SNT), 0, s, b, el);
+  });
+  return (int)hipGetLastError();
+}
+
+int launch_step_mixed(const DecodeArgs& a, const EvictArgs& e, const DecodeArgs& ac, const EvictArgs& el,
+                      int D, int G, void* stream) {
+  if (G != 4) return (int)hipErrorInvalidValue;
+  if (D == 128) return launch_step_mixed_t<128>(a, e, ac, el, (hipStream_t)stream);
+  if (D == 64) return launch_step_mixed_t<64>(a, e, ac, el, (hipStream_t)stream);
+  return (int)hipErrorInvalidValue;
 }
 
 template <int D>
