@@ -320,7 +320,9 @@ dc_status dc_decode_sample_evict(const dc_dims *dims, dc_kv *kv, dc_feat *feat,
  *             kept_out layout of dc_score_evict); needed for logp_out only
  *   logz_out, logp_out  [units] float64; either may be NULL
  * Computed in binary64 from the characteristic function of the subset size, exact
- * up to rounding: about 1e-13 of the terms that are summed (sum |s| / tau).  A
+ * up to rounding at any spread of finite scores: about 1e-13 of the terms that are
+ * summed (sum |s| / tau over the rows that the likely subsets hold; rows masked with a
+ * large finite score cost no digits as long as subsets without them exist).  A
  * non-finite score or a kept index outside [0, len) gives NaN for that unit.
  * Workspace: dc_subset_log_prob_workspace_bytes(units, len, budget) bytes
  * (zero unless K > 4096).

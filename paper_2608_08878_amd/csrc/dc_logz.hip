@@ -38,6 +38,15 @@
 // kernel's place, 117 M updates of seven instructions a unit, took 6390 us.  Error
 // of log Z against binary64: 6e-16 relative (the binary32 recursion: 2e-10).
 //
+// The search for t starts at the scores' mean and takes 2-3 Newton steps where the
+// scores have one scale (up to 16 for a spread of thousands).  Where no row lies near
+// the mean, or Newton does not arrive, search() goes on: from the mean of the rows on
+// B's side, then from the order statistics, whose bracket holds at any spread.
+// Measured (the call above, 64 rows of every unit masked with float32's lowest value,
+// -1e9, -1e4): 142 us each; Newton and bisection alone 2310 (without arriving), 311, 135.
+// B t enters the result only by the rows that the sum over x > 0 does not already
+// count, so a t in the middle of a wide gap costs no digits.
+//
 // One row kept or one row evicted (K = 1, the steady step) is a logsumexp over
 // the rows and skips all this.
 // Measured (2048 units of 2049 rows): 18-22 us, all of it latency (33 MB are
@@ -60,7 +69,9 @@ constexpr int NGRP = 4;                  // node groups (one wave each, or sever
 constexpr int NPG = 6;                   // nodes of a group, in threes
 constexpr int NMAX = NGRP * NPG;         // nodes at most (the bounds above give 21)
 constexpr int KR = 8;                    // rows a thread keeps in registers
-constexpr int MAX_IT = 200;              // steps of the search for t (2-3 usual, 16 seen)
+constexpr int NEWTON = 24;               // steps of the search for t from a mean of the scores (2-3 usual)
+constexpr int HALVINGS = 64;             // and from the order statistics
+constexpr double MASK_R = 1e4;           // -r of a row that the sum over all rows would lose digits to
 constexpr double PI = 0x1.921fb54442d18p+1;
 
 // Sizes of unit u (ragged caches and per-unit budgets: per unit).
@@ -98,6 +109,15 @@ __device__ __forceinline__ double exp_neg(double x) {
   y = __builtin_fma(y, f, 1.0);
   y = __builtin_fma(y, f, 1.0);
   return __builtin_amdgcn_ldexp(y, (int)k);
+}
+
+// float32 values (no NaN) as integers of the same order, and back
+__device__ __forceinline__ uint32_t order_key(float x) {
+  const uint32_t b = __float_as_uint(x);
+  return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
+}
+__device__ __forceinline__ float order_value(uint32_t k) {
+  return __uint_as_float(k ^ ((k >> 31) ? 0x80000000u : 0xFFFFFFFFu));
 }
 
 struct Add {
@@ -148,6 +168,120 @@ __device__ __forceinline__ void block_red(double (&x)[N], Op op, double* buf) {
     for (int w = 1; w < NW; ++w) v = op(v, buf[j * NW + w]);
     x[j] = v;
   }
+}
+
+// E[S] and its variance at t (relative to ref), with binary32 weights.
+template <int NT>
+__device__ __forceinline__ void moments(const float* s, int L, double itau, double ref, double t, double* red,
+                                        double& mean, double& var) {
+  float pm = 0.0f, pv = 0.0f;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < L; i += NT) {
+    const double y = (double)s[i] * itau - ref;
+    const float x = fminf(fmaxf((float)(y - t), -80.0f), 80.0f);
+    const float e = __builtin_amdgcn_exp2f(-fabsf(x) * 1.44269504088896340736f);
+    const float q = __builtin_amdgcn_rcpf(1.0f + e);
+    const float w = e * q;
+    pm += x >= 0.0f ? q : w;
+    pv = __builtin_fmaf(w, q, pv);
+  }
+  double v[2] = {(double)pm, (double)pv};
+  block_red<NT, 2>(v, Add(), red);
+  mean = v[0];
+  var = v[1];
+}
+__device__ __forceinline__ bool close_to(double mean, double var, int B) {
+  return fabs(mean - B) <= 0.25 * sqrt(var + 0.25);
+}
+__device__ __forceinline__ double newton(double t, double mean, double var, double lb, int L) {
+  double m = mean > 1e-30 ? mean : 1e-30;
+  m = m < L * (1.0 - 1e-7) ? m : L * (1.0 - 1e-7);
+  return t + (log(m / (L - m)) - lb) * m * (1.0 - m / L) / (var > 1e-30 ? var : 1e-30);
+}
+
+struct Search {
+  double ref, t, mean, var;
+  bool found;
+};
+
+// The search for t where the scores have several scales (rows masked with a large
+// finite value, say), so that Newton from their mean does not arrive: E[S] is `mean`
+// at t, relative to mx.  Ends with |E[S] - B| as close_to asks (found), at any spread.
+template <int NT>
+__device__ __forceinline__ Search search(const float* s, int L, int B, double itau, double mx, double mn,
+                                         double t, double mean, double* red) {
+  Search r = {mx, t, mean, 0.0, false};
+  double lo = mn - mx - 50.0, hi = 50.0, rl = -INFINITY, rh = INFINITY;
+  const double lb = log((double)B / (double)(L - B));
+  bool halve = false;
+  for (int it = 0; !r.found && it < NEWTON + HALVINGS; ++it) {
+    if (r.mean > B) lo = r.t;
+    else hi = r.t;
+    double next = r.t;
+    if (it == 0 || (it == 1 && r.var < 1e-6 * fabs(r.mean - B))) {
+      // the start again, from the mean of the rows on B's side of t (and of where
+      // that leads, once: masked rows are one group)
+      if (r.mean > B) rl = mx + r.t;
+      else rh = mx + r.t;
+      double n[3] = {0.0, 0.0, 0.0};      // rows in (rl, rh], their sum, rows above rh
+#pragma unroll 4
+      for (int i = threadIdx.x; i < L; i += NT) {
+        const double x = (double)s[i] * itau;
+        const bool in = x > rl && x <= rh;
+        n[0] += in ? 1.0 : 0.0;
+        n[1] += in ? x : 0.0;
+        n[2] += x > rh ? 1.0 : 0.0;
+      }
+      block_red<NT, 3>(n, Add(), red);
+      next = n[1] / n[0] - mx - log(((double)B - n[2]) / (n[0] + n[2] - (double)B));
+      next = next > lo && next < hi ? next : 0.5 * (lo + hi);
+    } else if (!halve && it < NEWTON) {
+      next = newton(r.t, r.mean, r.var, lb, L);
+      next = next > lo && next < hi ? next : 0.5 * (lo + hi);
+    }
+    if (!halve && next == r.t) {
+      // Many scales, or ties so far from the largest that t cannot be stated between
+      // them: from the order statistics.  s_(B), the B-th largest score, is the
+      // largest value that at least B scores reach: two bits of its key a pass.
+      uint32_t key = 0;
+      for (int sh = 30; sh >= 0; sh -= 2) {
+        int c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < L; i += NT) {
+          const uint32_t k = order_key(s[i]);
+          c1 += k >= (key | 1u << sh) ? 1 : 0;
+          c2 += k >= (key | 2u << sh) ? 1 : 0;
+          c3 += k >= (key | 3u << sh) ? 1 : 0;
+        }
+        double n[3] = {(double)c1, (double)c2, (double)c3};
+        block_red<NT, 3>(n, Add(), red);
+        key |= (n[2] >= B ? 3u : n[1] >= B ? 2u : n[0] >= B ? 1u : 0u) << sh;
+      }
+      // relative to r_(B): E[S] <= B - 1 + (L - B + 1) e^-t, so t is at most
+      // log(L - B + 1); and at r_(B+1) - x, E[S] >= (B + 1)(1 - e^-x), so it is at
+      // least r_(B+1) - r_(B) - log(B + 1).  The middle of a wide gap between the two
+      // is close enough, and a narrow bracket is halved: about 15 times at most.
+      double n[1] = {0.0};
+      float below = -INFINITY;
+      for (int i = threadIdx.x; i < L; i += NT) {
+        const float x = s[i];
+        const bool in = order_key(x) >= key;
+        n[0] += in ? 1.0 : 0.0;
+        below = in ? below : fmaxf(below, x);
+      }
+      block_red<NT, 1>(n, Add(), red);
+      double b[1] = {(double)below};
+      block_red<NT, 1>(b, Max(), red);
+      r.ref = (double)order_value(key) * itau;
+      lo = (n[0] > B ? 0.0 : b[0] * itau - r.ref) - log((double)B + 1.0) - 1.0;
+      hi = log((double)(L - B) + 1.0) + 1.0;
+      halve = true;
+    }
+    r.t = halve ? 0.5 * (lo + hi) : next;
+    moments<NT>(s, L, itau, r.ref, r.t, red, r.mean, r.var);
+    r.found = close_to(r.mean, r.var, B);
+  }
+  return r;
 }
 
 // (re, im) of the product of two complex numbers
@@ -248,42 +382,49 @@ __global__ void __launch_bounds__(NT, 4) logz_kernel(LogzArgs a) {
 #pragma unroll 2
     for (int i = tid + KR * NT; i < L; i += NT) add(s[i]);
     block_red<NT, 1>(e, Add(), red);
+    if (!one && c > MASK_R) {
+      // a masked row is far larger than the rows that count: sum r without one
+      // smallest r, as a sum over the others
+      double v[2] = {0.0, 0.0};             // sum of r, number of rows above mn
+      for (int i = tid; i < L; i += NT) {
+        const double r = (double)s[i] * itau;
+        v[0] += r > mn ? r : 0.0;
+        v[1] += r > mn ? 1.0 : 0.0;
+      }
+      block_red<NT, 2>(v, Add(), red);
+      finish(v[0] + ((double)(L - 1) - v[1]) * mn + log(e[0]));
+      return;
+    }
     finish((one ? 0.0 : sum) + c + log(e[0]));
     return;
   }
   if constexpr (!ONE) {
 
-  // t relative to the largest r: E[S] within a quarter of a standard deviation
-  // of B is enough, so binary32 weights do.  Newton on logit(E[S] / L), exact
-  // in one step for equal scores, inside a bracket that bisection halves.
+  // t, relative to ref: E[S] within a quarter of a standard deviation of B is
+  // enough, so binary32 weights do.  Newton on logit(E[S] / L), exact in one step
+  // for equal scores, inside a bracket that bisection halves.
+  double ref = mx, mean, var;
   double lo = mn - mx - 50.0, hi = 50.0;
   const double lb = log((double)B / (double)(L - B));
   double t = sum / L - mx - lb;
   t = t > lo && t < hi ? t : 0.5 * (lo + hi);
-  double mean, var;
+  bool found = false;
   for (int it = 0;; ++it) {
-    float pm = 0.0f, pv = 0.0f;
-#pragma unroll 8
-    for (int i = tid; i < L; i += NT) {
-      const double y = (double)s[i] * itau - mx;
-      const float x = fminf(fmaxf((float)(y - t), -80.0f), 80.0f);
-      const float e = __builtin_amdgcn_exp2f(-fabsf(x) * 1.44269504088896340736f);
-      const float q = __builtin_amdgcn_rcpf(1.0f + e);
-      const float w = e * q;
-      pm += x >= 0.0f ? q : w;
-      pv = __builtin_fmaf(w, q, pv);
-    }
-    double v[2] = {(double)pm, (double)pv};
-    block_red<NT, 2>(v, Add(), red);
-    mean = v[0];
-    var = v[1];
-    if (fabs(mean - B) <= 0.25 * sqrt(var + 0.25) || it >= MAX_IT) break;
+    moments<NT>(s, L, itau, ref, t, red, mean, var);
+    found = close_to(mean, var, B);
+    if (found || it >= NEWTON || (it == 0 && var < 1e-6 * fabs(mean - B))) break;
     if (mean > B) lo = t;
     else hi = t;
-    double m = mean > 1e-30 ? mean : 1e-30;
-    m = m < L * (1.0 - 1e-7) ? m : L * (1.0 - 1e-7);
-    const double step = (log(m / (L - m)) - lb) * m * (1.0 - m / L) / (var > 1e-30 ? var : 1e-30);
-    t = t + step > lo && t + step < hi ? t + step : 0.5 * (lo + hi);
+    const double next = newton(t, mean, var, lb, L);
+    t = next > lo && next < hi ? next : 0.5 * (lo + hi);
+  }
+  if (!found) {
+    const Search r = search<NT>(s, L, B, itau, mx, mn, t, mean, red);
+    found = r.found;
+    ref = r.ref;
+    t = r.t;
+    mean = r.mean;
+    var = r.var;
   }
 
   // nodes (M odd: they come in conjugate pairs around the zeroth)
@@ -295,6 +436,7 @@ __global__ void __launch_bounds__(NT, 4) logz_kernel(LogzArgs a) {
     const int n = (int)ceil(acos(1.0 - cut) * M / (2.0 * PI));
     N = n < N ? n : N;
   }
+  found = found && N <= NMAX;
   N = N < NMAX ? N : NMAX;
   if (tid < NMAX) {
     const double h = PI * (double)(tid + 1) / (double)M;   // half the node's angle
@@ -321,7 +463,8 @@ __global__ void __launch_bounds__(NT, 4) logz_kernel(LogzArgs a) {
   Cplx acc[NPG];
 #pragma unroll
   for (int k = 0; k < NPG; ++k) acc[k] = {1.0, 0.0};
-  double base = 0.0, prod = 1.0;          // sum of max(x, 0), product of 1 + e^-|x| <= 2
+  double base = 0.0, prod = 1.0;          // sum of r over x > 0, product of 1 + e^-|x| <= 2
+  int npos = 0;                           // rows with x > 0
   const int nch = (L + CHUNK - 1) / CHUNK;
   const int G4 = (L + 4 * nch - 1) / (4 * nch);            // groups of a chunk (<= CHUNK / 4)
   for (int c0 = 0; c0 < L; c0 += 4 * G4) {
@@ -336,13 +479,15 @@ __global__ void __launch_bounds__(NT, 4) logz_kernel(LogzArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const bool ok = c0 + g + j * G4 < L;
-        const double x = ((double)v[j] * itau - mx) - t;
+        const double r = (double)v[j] * itau, x = (r - ref) - t;
         const double e = exp_neg(-fabs(x)), w = 1.0 + e;
         double q = __builtin_amdgcn_rcp(w);                // 1 / w, w in [1, 2]: two Newton steps
         q = __builtin_fma(__builtin_fma(-w, q, 1.0), q, q);
         q = __builtin_fma(__builtin_fma(-w, q, 1.0), q, q);
         p[j] = !ok ? 0.0 : x >= 0.0 ? q : e * q;
-        base += ok && x > 0.0 ? x : 0.0;
+        const bool pos = ok && x > 0.0;
+        base += pos ? r : 0.0;
+        npos += pos ? 1 : 0;
         prod *= ok ? w : 1.0;
       }
       const double a1 = p[0] + p[1], a2 = p[0] * p[1], b1 = p[2] + p[3], b2 = p[2] * p[3];
@@ -407,14 +552,16 @@ __global__ void __launch_bounds__(NT, 4) logz_kernel(LogzArgs a) {
     const double th = 2.0 * PI * (double)(int)(((int64_t)(tid + 1) * B) % M) / (double)M;
     term[tid] = __builtin_fma(c.re, cos(th), c.im * sin(th));
   }
-  double v[2] = {base, log(prod)};
-  block_red<NT, 2>(v, Add(), red);        // (its barriers also publish term)
+  double v[3] = {base, log(prod), (double)npos};
+  block_red<NT, 3>(v, Add(), red);        // (its barriers also publish term)
   if (tid == 0) {
     double ps = 1.0;
     for (int k = 0; k < N; ++k) ps = ps + 2.0 * term[k];
-    // (scores so far apart that t cannot reach B: the smallest probability)
-    const double p = ps > 0.0 ? ps / (double)M : 0x1p-1022;
-    finish((double)B * mx + (v[0] + v[1]) + (double)B * t + log(p));
+    // (a search without its end or a node sum that is no probability: neither occurs)
+    const bool ok = found && ps > 0.0;
+    // B t + sum max(x, 0), without the t that every row above it shares (in the
+    // middle of a gap t may be far larger than the rows that count)
+    finish(ok ? v[0] + ((double)B - v[2]) * (ref + t) + v[1] + log(ps / (double)M) : __builtin_nan(""));
   }
   }
 }

@@ -124,6 +124,37 @@ def test_log_partition_is_exact_to_binary64(units, L, B_, scale):
         assert abs(lp[u] - refp) <= tol, (u, lp[u], refp, tol)
 
 
+# Rows masked with a finite value: as many as leave exactly, just fewer or just more
+# rows than the budget, with the budget on both sides of L / 2, one row kept or evicted,
+# and in both workgroup sizes.
+F32_MIN = float(np.finfo(np.float32).min)
+MASKED = [(3, 1025, 64, 256), (3, 1025, 1, 256), (300, 1025, 64, 900), (3, 1025, 512, 512), (3, 1025, 512, 513),
+          (3, 1025, 512, 514), (300, 1025, 768, 256), (3, 1025, 1000, 256), (3, 1025, 1, 1024), (300, 1025, 1, 1023),
+          (3, 1025, 64, 1), (3, 61, 30, 20), (3, 61, 58, 3), (3, 61, 59, 3), (3, 5000, 700, 1500)]
+
+
+@pytest.mark.parametrize("mask", [F32_MIN, -1e35, -1e30, -1e9, 1e30])
+def test_log_partition_of_rows_masked_with_a_finite_score(mask):
+    for units, L, masked, B_ in MASKED:
+        s = _scores(units, L, 1.0, step=L + masked)
+        for u in range(units):
+            s[u, np.random.default_rng(u).permutation(L)[:masked]] = mask
+        kept = np.argsort(-s, axis=1, kind="stable")[:, :B_].astype(np.int32)
+        print(f"logz masked L={L} B={B_} units={units}: {masked} rows at {mask}", flush=True)
+        lz, lp = subset_log_prob(_dev(s), B_, 1.0, kept=_dev(kept, torch.int32))
+        torch.cuda.synchronize()
+        lz, lp = lz.cpu().numpy(), lp.cpu().numpy()
+        for u in sorted({0, 1, units - 1}):
+            r = s[u].astype(np.float64)
+            ref = osmp.log_partition(r, B_)
+            # binary64 rounding of L additions on either side: of the rows that are not
+            # masked, and of the masked ones only where the result holds some
+            tol = 4 * (L + 64) * 2.0 ** -52 * (np.abs(r[s[u] != np.float32(mask)]).sum() + L + abs(ref))
+            assert abs(lz[u] - ref) <= tol, (units, L, masked, B_, u, lz[u], ref, tol)
+            refp = r[kept[u]].sum() - ref
+            assert abs(lp[u] - refp) <= tol, (units, L, masked, B_, u, lp[u], refp, tol)
+
+
 def test_log_partition_special_rows():
     L = 400
     rows = [np.full(L, 0.37, np.float32),                               # all equal
