@@ -673,7 +673,7 @@ dc_status dc_decode_evict_units(const dc_dims* dims, dc_kv* kv, dc_feat* feat,
       ac.fused_rows = af.L;
       dc::EvictArgs el = e;
       el.fused_rows = af.L;
-      if (G == 4) {
+      if (dc::step_mixed_fits(ac.units, ac.nchunks, G)) {
         if (dc::launch_step_mixed(af, ef, ac, el, D, G, hip_stream) != 0) return DC_ERR_HIP;
         el.len_add = a.append;
         if (dc::launch_select_keys(el, dc::step_keys(ac), ac.lmax, D, hip_stream) != 0) return DC_ERR_HIP;

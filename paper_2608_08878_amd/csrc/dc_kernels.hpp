@@ -185,6 +185,7 @@ int launch_step(const DecodeArgs& a, const EvictArgs* e, int D, int G, bool feat
                 void* stream);
 // A ragged step with per-unit budgets: the units that fit on chip (a, e) and the
 // longer units' chunks (ac) in one launch, then the latter's features and keys (el).
+bool step_mixed_fits(int units, int nchunks, int G);
 int launch_step_mixed(const DecodeArgs& a, const EvictArgs& e, const DecodeArgs& ac, const EvictArgs& el,
                       int D, int G, void* stream);
 inline const uint64_t* step_keys(const DecodeArgs& a) { return (const uint64_t*)a.ws_r; }

@@ -1172,20 +1172,25 @@ static int launch_step_t(const DecodeArgs& a, const EvictArgs* e, bool feat, boo
   return (int)hipGetLastError();
 }
 
+// The two kinds of workgroup share a launch for the group size whose chunks need no
+// more registers than the unit kernel (G = 8: 202 a thread).
+bool step_mixed_fits(int units, int nchunks, int G) {
+  return G == 4 && (long)units * (1 + nchunks) <= 1l << 30;
+}
+
 // The ragged step in one launch for the decode of all units, then the features and
-// scores of the longer ones; hipErrorInvalidValue where the two do not share a CU's
-// LDS and registers (the caller takes two launches).
+// scores of the longer ones.
 template <int D>
 static int launch_step_mixed_t(const DecodeArgs& a, const EvictArgs& e, const DecodeArgs& ac,
                                const EvictArgs& el, hipStream_t s) {
   constexpr int G = 4;
+  // (a.L is at most step_ragged_rows: half the LDS)
+  static_assert(sizeof(ChunkLds<D, G>) <= (size_t)S_LDS / 2, "two workgroups of either kind per CU");
   size_t lds = step_lds_bytes(a.L, G, D, true, 0);
   lds = lds > sizeof(ChunkLds<D, G>) ? lds : sizeof(ChunkLds<D, G>);
-  const long blocks = (long)a.units * (1 + ac.nchunks);
-  if (lds > (size_t)S_LDS / 2 || blocks > (1l << 30)) return (int)hipErrorInvalidValue;
   auto pick = [&](auto kern) {
     allow_lds((const void*)kern, lds);
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(SNT), lds, s, a, e, ac);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.units * (1 + ac.nchunks))), dim3(SNT), lds, s, a, e, ac);
   };
   const bool early = step_early(a, G);
   if (ac.retire) early ? pick(step_mixed_kernel<D, G, true, true>) : pick(step_mixed_kernel<D, G, true, false>);
@@ -1200,7 +1205,7 @@ static int launch_step_mixed_t(const DecodeArgs& a, const EvictArgs& e, const De
 
 int launch_step_mixed(const DecodeArgs& a, const EvictArgs& e, const DecodeArgs& ac, const EvictArgs& el,
                       int D, int G, void* stream) {
-  if (G != 4) return (int)hipErrorInvalidValue;
+  if (!step_mixed_fits(a.units, ac.nchunks, G)) return (int)hipErrorInvalidValue;
   if (D == 128) return launch_step_mixed_t<128>(a, e, ac, el, (hipStream_t)stream);
   if (D == 64) return launch_step_mixed_t<64>(a, e, ac, el, (hipStream_t)stream);
   return (int)hipErrorInvalidValue;

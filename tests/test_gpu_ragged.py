@@ -184,15 +184,15 @@ def test_units_that_keep_every_row_are_not_scored_without_scores_out(hidden):
                 assert np.array_equal(H.to_np(kept[1][u])[:lens[0][u]], np.arange(lens[0][u]))
 
 
-def _fused_ragged_run(pattern, steps, n0, batch=32):
+def _fused_ragged_run(pattern, steps, n0, batch=32, group=4, **kw):
     """dc_decode_evict_units (one call per step) on free-running device and oracle
     trajectories, on enough units for the single-launch route (unit u keeps the
     budget of KV head u mod len(pattern)); the oracle follows unit 0, the last
     unit and six seeded random units: attention output, scores, the slot map
     (exactly, under the oracle's selection and compaction of the GPU's scores),
     lengths and the post-step state, until a selection lands in the near-tie band."""
-    wl = W.WORKLOADS[2].scaled(batch=batch, n_kv_heads=len(pattern), n_q_heads=4 * len(pattern),
-                               n0=n0, budget=max(pattern), steps=steps)
+    wl = W.WORKLOADS[2].scaled(batch=batch, n_kv_heads=len(pattern), n_q_heads=group * len(pattern),
+                               n0=n0, budget=max(pattern), steps=steps, **kw)
     U = wl.units
     assert U >= 128
     budgets = [pattern[u % len(pattern)] for u in range(U)]
@@ -265,6 +265,77 @@ def test_one_call_ragged_step_with_long_full_cache_units():
     # compresses every unit through the chunked decode and the stand-alone selection;
     # then the budgeted units run in one launch and the full-cache units on the chunked path
     assert _fused_ragged_run([200, 10 ** 6, 150, 10 ** 6], steps=70, n0=4600) >= 1
+
+
+# Units longer than the single-launch bound (G = 4: 4479 rows of 128, 4735 of 64; G = 8:
+# 1983 and 2239) that evict a row on every step, beside units that never do and short
+# ones, through the retire of a four-step window.  More than 256 units: the other
+# variant of the launch that holds both kinds (G = 4); G = 8 takes two launches.
+LONG_UNITS = [(4800, 4900, 32, 4, 128), (4800, 4900, 72, 4, 128), (5000, 5100, 32, 4, 64), (5000, 5100, 72, 4, 64),
+              (2100, 2200, 32, 8, 128), (2400, 2500, 72, 8, 64)]
+
+
+@pytest.mark.parametrize("budget,n0,batch,group,head_dim", LONG_UNITS)
+def test_one_call_ragged_step_with_long_evicting_units(budget, n0, batch, group, head_dim):
+    assert _fused_ragged_run([200, budget, 150, 10 ** 6], 8, n0, batch, group, head_dim=head_dim,
+                             ent_window=4) >= 1
+
+
+@pytest.mark.parametrize("units", [4, 160])
+@pytest.mark.parametrize("sampled", [True, False])
+def test_one_budget_steps_of_a_ragged_cache(units, sampled):
+    """dc_decode_sample_evict and dc_decode_evict on units of different lengths: every
+    kernel of the call, the log-partition among them, counts the appended row that the
+    stored lengths do not hold yet."""
+    first, budget, tau, seed = [120, 700, 90, 400], 300, 0.8, 91
+    wl = W.WORKLOADS[2].scaled(batch=units // 4, n_kv_heads=4, n_q_heads=16, n0=800, budget=700, steps=4)
+    U = wl.units
+    assert U == units
+    buf = DecodeBuffers(wl.batch, wl.n_layers, wl.n_q_heads, wl.n_kv_heads, wl.head_dim, wl.capacity, wl.dtype,
+                        wl.ent_window, 0.0, True, ragged=True)
+    buf.reserve_workspace(wl.capacity)
+    sg.init_cache(wl, buf.k, buf.v, U, buf.cap)
+    buf.feat_init(wl.n0, 0)
+    _, pol = _policy(wl)
+    q, kn, vn = _step_tensors(wl)
+    sg.queries(wl, 0, q)
+    sg.new_rows(wl, 0, kn, vn, U)
+    bud = torch.tensor([first[u % 4] for u in range(U)], dtype=torch.int32, device="cuda")
+    buf.decode_evict_units(pol, bud, max(first), q, kn, vn)
+    lens = np.array([first[u % 4] for u in range(U)])
+    for t in range(1, wl.steps):
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_np(buf.unit_len).astype(int), lens), t
+        pos = [np.append(H.to_np(buf.pos[u, :lens[u]]).astype(np.int64), wl.n0 + t) for u in range(U)]
+        sg.queries(wl, t, q)
+        sg.new_rows(wl, t, kn, vn, U)
+        Lb = buf.kv.len + 1
+        scores = torch.full((U, Lb), float("nan"), dtype=torch.float32, device="cuda")
+        kept = torch.empty((U, min(budget, Lb)), dtype=torch.int32, device="cuda")
+        logp = torch.empty(U, dtype=torch.float64, device="cuda")
+        print(f"ragged step {t}: {U} units, bound {Lb}, sampled {sampled}", flush=True)
+        if sampled:
+            buf.decode_sample_evict(pol, budget, B.make_gumbel(tau, seed, t), q, kn, vn, scores_out=scores,
+                                    kept_out=kept, logp_out=logp)
+        else:
+            buf.decode_evict(pol, budget, q, kn, vn, scores_out=scores, kept_out=kept)
+        torch.cuda.synchronize()
+        sc, kp, lp = H.to_np(scores), H.to_np(kept), logp.cpu().numpy()
+        for u in range(U):
+            L, nk = lens[u] + 1, min(budget, lens[u] + 1)
+            assert np.all(np.isfinite(sc[u, :L])), (t, u)
+            post = H.to_np(buf.pos[u, :nk]).astype(np.int64)
+            if sampled:
+                ok, _, amb, flips = _sampled_check(sc[u, :L], pos[u], post, budget, tau, seed, u, t)
+                assert ok, (t, u, amb, flips)
+                assert np.array_equal(kp[u, :nk], H.slot_map_of(np.sort(kp[u, :nk]), L)), (t, u)
+                ref = osmp.log_prob(sc[u, :L], kp[u, :nk], budget, tau)
+                assert abs(lp[u] - ref) <= _logz_tol(L, budget), (t, u, lp[u], ref)
+            else:
+                assert np.array_equal(kp[u, :nk], H.oracle_slot_map(sc[u, :L], pos[u], budget)), (t, u)
+            assert np.array_equal(post, pos[u][kp[u, :nk]]), (t, u)
+            lens[u] = nk
+        assert np.array_equal(H.to_np(buf.unit_len).astype(int), lens), t
 
 
 def test_one_call_ragged_step_equals_the_uniform_single_launch_step():
