@@ -914,12 +914,17 @@ __global__ void __launch_bounds__(SNT, 4) step_mixed_kernel(DecodeArgs a, EvictA
 // the state (28 B a row).  A row's key takes the place of its retired pair, which
 // only this thread reads (8 B a row at row stride lmax).  Rows are requested before
 // the chunks' sums are combined, one thread per head combines (not every thread
-// all heads), and a thread's rows share the policy's weights.  Measured per step
+// all heads).  FEW: all of a thread's rows at once, sharing the policy's weights, for
+// grids of at most three workgroups a CU; a larger one takes a row at a time in half
+// the registers (G = 4: 51 for 91), where the waves in flight hide the loads: 1024
+// units of 16001 rows that keep every row 315 -> 265 us (G = 8 416 -> 365), steps of
+// 104-127 units of 8193 rows 2-5 % less; the 480 workgroups of a scoring step of 40
+// units take 4 % longer by it, so they stay with the first.  Measured per step
 // (decode, scores, selection), with a scoring pass of its own -> here: 8 units of
 // 4097 rows 46.7 -> 30.1 us, of 12001 60.1 -> 42.6, 64 of 4097 67.8 -> 54.5; this
 // kernel and the scoring pass on 1024 units of 16385 rows 395 -> 299 us.
-template <int D, int G, bool FEAT, bool SCORE>
-__global__ void __launch_bounds__(SNT) stepc_d_kernel(DecodeArgs a, EvictArgs e) {
+template <int D, int G, bool FEAT, bool SCORE, bool FEW>
+__global__ void __launch_bounds__(SNT, FEW || !FEAT ? 1 : G > 4 ? 6 : 8) stepc_d_kernel(DecodeArgs a, EvictArgs e) {
   static_assert(FEAT || !SCORE, "scores need the features");
   __shared__ float newnorm_slot;
   __shared__ float comb[3][G];          // M, 1 / l, H
@@ -933,16 +938,16 @@ __global__ void __launch_bounds__(SNT) stepc_d_kernel(DecodeArgs a, EvictArgs e)
   const size_t ub = (size_t)u * a.cap;
   const float* s_src = FEAT ? a.ws_s + (size_t)u * a.lmax * G : nullptr;
   float* r_src = FEAT ? a.ws_r + (size_t)u * a.lmax * 2 : nullptr;
-  // this thread's rows r0 + tid + k SNT, all requested before the chunks' sums
-  // are combined (rows past r1 re-read the last one, unused)
-  constexpr int RB = SCHUNK / SNT;
+  // this thread's rows i0 + tid + k SNT, RB at a time (rows past r1 re-read the
+  // last one, unused); the first are requested before the chunks' sums are combined
+  constexpr int RB = FEW ? SCHUNK / SNT : 1;
   RowState x[RB];
   float sj[RB][G];
   float2 ret[RB] = {};
-  if (FEAT && r0 < r1) {
+  auto request = [&](int i0) {
 #pragma unroll
     for (int k = 0; k < RB; ++k) {
-      const int i = r0 + tid + k * SNT, ic = i < r1 ? i : r1 - 1;
+      const int i = i0 + tid + k * SNT, ic = i < r1 ? i : r1 - 1;
       load_row_state(a, ub + ic, x[k]);
       if constexpr (G >= 4) {
 #pragma unroll
@@ -957,7 +962,8 @@ __global__ void __launch_bounds__(SNT) stepc_d_kernel(DecodeArgs a, EvictArgs e)
       }
       if (a.retire) ret[k] = *reinterpret_cast<const float2*>(r_src + 2 * (size_t)ic);
     }
-  }
+  };
+  if (FEAT && r0 < r1) request(r0);
   // chunk c's sums move to the common maximum M: with f = e^(m_c - M),
   // l += f l_c, u += f (u_c + (m_c - M) l_c), o += f o_c (a neutral chunk: f = 0);
   // one thread per head, the chunks in order
@@ -1008,33 +1014,45 @@ __global__ void __launch_bounds__(SNT) stepc_d_kernel(DecodeArgs a, EvictArgs e)
     H[j] = comb[2][j];
   }
   if constexpr (FEAT) {
+    auto update = [&](int i0) {
 #pragma unroll
-    for (int k = 0; k < RB; ++k) {
-      const int i = r0 + tid + k * SNT;
-      if (i >= r1) continue;
-      float pj[G];
+      for (int k = 0; k < RB; ++k) {
+        const int i = i0 + tid + k * SNT;
+        if (i >= r1) continue;
+        float pj[G];
 #pragma unroll
-      for (int j = 0; j < G; ++j) pj[j] = __builtin_amdgcn_exp2f((sj[k][j] - M[j]) * LOG2E);
-      update_row<G>(a, ub + i, i == newrow, pj, invl, H, ret[k], newnorm, x[k]);
-    }
-    if constexpr (SCORE) {
-      // (a unit that keeps every row needs no key; past the last row of a chunk
-      // the state is that of its last row)
-      if (r0 < r1 && (e.scores_out || unit_budget(e, u) < Lu)) {
-        const float invT = 1.0f / (float)a.T;
-        float f[RB][4], sc[RB];
+        for (int j = 0; j < G; ++j) pj[j] = __builtin_amdgcn_exp2f((sj[k][j] - M[j]) * LOG2E);
+        update_row<G>(a, ub + i, i == newrow, pj, invl, H, ret[k], newnorm, x[k]);
+      }
+    };
+    auto score = [&](int i0) {            // (past the last row of a chunk the state is that of its last row)
+      const float invT = 1.0f / (float)a.T;
+      float f[RB][4], sc[RB];
 #pragma unroll
-        for (int k = 0; k < RB; ++k) make_features(x[k].al, x[k].vn, x[k].nu, x[k].de, x[k].p, invT, f[k]);
-        const int rows = (r1 - r0 + SNT - 1) / SNT;
-        policy_scores<RB>(e, f, sc, rows);
+      for (int k = 0; k < RB; ++k) make_features(x[k].al, x[k].vn, x[k].nu, x[k].de, x[k].p, invT, f[k]);
+      policy_scores<RB>(e, f, sc, (r1 - i0 + SNT - 1) / SNT);
 #pragma unroll
-        for (int k = 0; k < RB; ++k) {
-          const int i = r0 + tid + k * SNT;
-          if (i >= r1) continue;
-          if (e.scores_out) e.scores_out[(size_t)u * e.L + i] = sc[k];
-          reinterpret_cast<uint64_t*>(r_src)[i] =
-              row_key(e.sample ? sampled_score(e, sc[k], x[k].p, u) : sc[k], x[k].p);
-        }
+      for (int k = 0; k < RB; ++k) {
+        const int i = i0 + tid + k * SNT;
+        if (i >= r1) continue;
+        if (e.scores_out) e.scores_out[(size_t)u * e.L + i] = sc[k];
+        reinterpret_cast<uint64_t*>(r_src)[i] =
+            row_key(e.sample ? sampled_score(e, sc[k], x[k].p, u) : sc[k], x[k].p);
+      }
+    };
+    // (a unit that keeps every row needs no key)
+    const bool scored = SCORE && (e.scores_out || unit_budget(e, u) < Lu);
+    if constexpr (FEW) {                  // one batch is a chunk
+      update(r0);
+      if constexpr (SCORE)
+        if (r0 < r1 && scored) score(r0);
+    } else {
+#pragma unroll 1
+      for (int i0 = r0; i0 < r1; i0 += SNT) {
+        if (i0 > r0) request(i0);
+        update(i0);
+        if constexpr (SCORE)
+          if (scored) score(i0);
       }
     }
   }
@@ -1163,10 +1181,13 @@ static int launch_step_t(const DecodeArgs& a, const EvictArgs* e, bool feat, boo
       DecodeArgs b = a;
       b.y0 = y0;
       const EvictArgs none = {};
-      const dim3 grid(a.nchunks, ny);
-      if (feat && e) hipLaunchKernelGGL((stepc_d_kernel<D, G, true, true>), grid, dim3(SNT), 0, s, b, *e);
-      else if (feat) hipLaunchKernelGGL((stepc_d_kernel<D, G, true, false>), grid, dim3(SNT), 0, s, b, none);
-      else hipLaunchKernelGGL((stepc_d_kernel<D, G, false, false>), grid, dim3(SNT), 0, s, b, none);
+      const bool few = (long)a.units * a.nchunks <= 768;
+      auto pick = [&](auto kern, const EvictArgs& ev) {
+        hipLaunchKernelGGL(kern, dim3(a.nchunks, ny), dim3(SNT), 0, s, b, ev);
+      };
+      if (!feat) few ? pick(stepc_d_kernel<D, G, false, false, true>, none) : pick(stepc_d_kernel<D, G, false, false, false>, none);
+      else if (e) few ? pick(stepc_d_kernel<D, G, true, true, true>, *e) : pick(stepc_d_kernel<D, G, true, true, false>, *e);
+      else few ? pick(stepc_d_kernel<D, G, true, false, true>, none) : pick(stepc_d_kernel<D, G, true, false, false>, none);
     });
   }
   return (int)hipGetLastError();
@@ -1198,7 +1219,10 @@ static int launch_step_mixed_t(const DecodeArgs& a, const EvictArgs& e, const De
   for_grid_y(ac.units, [&](int y0, int ny) {
     DecodeArgs b = ac;
     b.y0 = y0;
-    hipLaunchKernelGGL((stepc_d_kernel<D, G, true, true>), dim3(ac.nchunks, ny), dim3(SNT), 0, s, b, el);
+    // (most chunks are those of units served above and leave at once)
+    auto kern = (long)ac.units * ac.nchunks <= 2048 ? stepc_d_kernel<D, G, true, true, true>
+                                                    : stepc_d_kernel<D, G, true, true, false>;
+    hipLaunchKernelGGL(kern, dim3(ac.nchunks, ny), dim3(SNT), 0, s, b, el);
   });
   return (int)hipGetLastError();
 }

@@ -270,9 +270,10 @@ def test_one_call_ragged_step_with_long_full_cache_units():
 # Units longer than the single-launch bound (G = 4: 4479 rows of 128, 4735 of 64; G = 8:
 # 1983 and 2239) that evict a row on every step, beside units that never do and short
 # ones, through the retire of a four-step window.  More than 256 units: the other
-# variant of the launch that holds both kinds (G = 4); G = 8 takes two launches.
-LONG_UNITS = [(4800, 4900, 32, 4, 128), (4800, 4900, 72, 4, 128), (5000, 5100, 32, 4, 64), (5000, 5100, 72, 4, 64),
-              (2100, 2200, 32, 8, 128), (2400, 2500, 72, 8, 64)]
+# variant of the launch that holds both kinds (G = 4); G = 8 takes two launches.  768
+# and 416 units: features and scores a row at a time.
+LONG_UNITS = [(4800, 4900, 32, 4, 128), (4800, 4900, 72, 4, 128), (4800, 4900, 192, 4, 128), (5000, 5100, 32, 4, 64),
+              (5000, 5100, 72, 4, 64), (2100, 2200, 32, 8, 128), (2100, 2200, 104, 8, 128), (2400, 2500, 72, 8, 64)]
 
 
 @pytest.mark.parametrize("budget,n0,batch,group,head_dim", LONG_UNITS)
