@@ -69,9 +69,14 @@ size_t split_bytes(const dc_dims* d, int L) {
 // in flight allow, so the chunk is the one (a multiple of 128 rows: two tiles per
 // wave at 256) whose fullest CU has the fewest rows to stream, a chunk costing
 // about 160 rows of its own and 56 in the combination; at most 16 chunks, and no
-// more than the workspace has room for.  Measured per step, against about 512 workgroups of 512
-// rows or more: 64 units of 4097 rows 54.2 -> 50.0 us, 32 45.2 -> 37.1, 48 47.2 -> 42.9, of
-// 3073 45.0 -> 37.6, 8 of 1025 27.0 -> 23.9.
+// more than the workspace has room for.  Measured per step, against about 512
+// workgroups of 512 rows or more: 64 units of 4097 rows 54.2 -> 50.0 us, 32 45.2 -> 37.1,
+// 48 47.2 -> 42.9, of 3073 45.0 -> 37.6, 8 of 1025 27.0 -> 23.9.
+// A last chunk of a few rows (a context of a power of two and the appended row) is not
+// one more for over 96 units, where two or more chunks share a CU and a quarter of the
+// small ones finds room: 104 units of 8193 rows decode in 80.6 us in chunks of 2048
+// rows, in 90.9 in the 1280 of the rule without this, 120 in 87.4 and 92.3, of rows of
+// 64 elements 51.6 and 59.3; 56 units lose 8 % by it.
 int chunk_rows(const dc_dims* d, int L) {
   const int full = dc::decode_chunk_rows();
   const long U = (long)units_of(d);
@@ -84,7 +89,9 @@ int chunk_rows(const dc_dims* d, int L) {
   for (int c = full; c >= MIN_CHUNK; c -= 128) {
     const long n = (L + c - 1) / c;
     if (c < full && (n > 16 || n > most)) break;
-    const long cost = ((U * n + CUS - 1) / CUS) * (c + 160) + 56 * n;
+    const long nf = L / c, qf = (U * nf + CUS - 1) / CUS;
+    const bool bit = U > 96 && L % c > 0 && L % c <= 64 && qf >= 2 && 4 * (qf * CUS - U * nf) >= U;
+    const long cost = (bit ? qf * (c + 160) + 200 : ((U * n + CUS - 1) / CUS) * (c + 160)) + 56 * n;
     if (c == full || cost < least) {
       least = cost;
       best = c;
