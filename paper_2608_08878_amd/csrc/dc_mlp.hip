@@ -221,9 +221,8 @@ score_mlp2_kernel(EvictArgs a, uint64_t* keys, int kstride) {
     // layer 1 on the matrix cores: per 16-unit block b, D = W1 x X^T with the
     // inputs padded to 32 (lanes kg > 0 supply zeros), so lane (ri, kg) gets
     // units 16 b + 4 kg + r of its row ri, accumulated onto their biases.
-    // Padded units (k >= h1) have zero weights, bias, gain and shift, so they
-    // come out exactly 0 here, after the LayerNorm and after the ReLU: only
-    // the variance sum needs a mask (none when FULL).
+    // Padded units (k >= h1) have zero weights and bias, so they come out exactly 0
+    // here and after the ReLU.
     typedef __attribute__((address_space(3))) const f32x4_v lfloat4;
     typedef __attribute__((address_space(3))) const bf16x8_t lbf16x8;
     bf16x8_t xh, xm, xl;
@@ -336,14 +335,25 @@ score_mlp2_kernel(EvictArgs a, uint64_t* keys, int kstride) {
 // holds input s mod 5 of part pair s / 5 in (xh wh, xm wh, xl wh, xh wm, xm wm,
 // xh wl).
 //
-// Layer 2: behind the LayerNorm |h| <= |gain| sqrt(h1) + |shift|, so one power
-// of two per network puts the activations into float16's range, and one the
-// weights: x = xh + xl in two float16 parts (11 significand bits each, signed
-// residual), all four part products kept.  The low ones are accumulated first,
+// Layer 2: behind the LayerNorm and the ReLU an activation is at most |gain| sqrt(h1)
+// + shift, so a power of two per hidden unit puts it into float16's range and its
+// inverse goes to the unit's column of W2: x = xh + xl in two float16 parts (11
+// significand bits each, signed residual), all four part products kept.  What a unit's
+// products lack of the largest unit's is shared evenly by the two scales, so that
+// neither side reaches float16's subnormal range before the products lie 2^30 below the
+// largest; a unit that its shift keeps off has no weights.  (With one scale for all, a
+// unit of gain 1e8 cost the others 13 bits.)  The low products are accumulated first,
 // over all k, and the high ones onto their sum: four roundings at the size of
-// the result instead of 24, so the error against binary64 is a tenth smaller
-// than the bf16 split's with six products (rms 7.3e-8 against 8.0e-8 of the
-// result, 128 terms).  Three products would not be: 8.4e-8.
+// the result instead of 24, so the error against binary64 is below the bf16 split's
+// with six products (rms, 128 units, in 2^-24 of the result: 1.73 and 1.84 for four and
+// five inputs against 2.07 and 2.43; the same for gains of 1e6 and 1e8 in single units;
+// 3.0 against 1.6 where one unit outweighs all others 1e9 times and is off).
+// Networks of at most 64 units have fewer terms to round: there the weights have a
+// third part, split from binary64, and the products of layer 1's high parts have an
+// instruction of their own (its adder aligns a block's products to the largest).
+// 64 units 1.31 and 1.50 against 1.50 and 1.64, 32 1.42 and 1.32 against 1.42 and 1.26;
+// without the two 1.55, 1.67, 1.71 and 1.56, for a tenth to a sixth less time (1024 x
+// 4097 rows, 64-64: 191 -> 223 us; six bf16 products 306).
 //
 // What bounds it: the sum of matrix and vector instructions, which do not overlap
 // on a SIMD here (counters: 559 k MFMA cycles + 500 k vector cycles of 1067 k; a
@@ -383,17 +393,15 @@ struct LayN {
   static constexpr int O_B2 = O_B1 + 3 * HP;          // b2, g2, be2, wo           [HP] each
   static constexpr int O_C = O_B2 + 4 * HP;           // 1 / (activation scale x weight scale)
   static constexpr int FLOATS = O_C + 4;
-  static constexpr int O_W2 = FLOATS * 4;             // bytes: parts h, l, [2][HP][RS]
-  static constexpr int O_W1 = O_W2 + 2 * HP * RS;     // bytes: [HP][RS1]
+  static constexpr int WP = HP == 64 ? 3 : 2;         // parts of a weight
+  static constexpr int O_W2 = FLOATS * 4;             // bytes: parts h, l (, ll), [WP][HP][RS]
+  static constexpr int O_W1 = O_W2 + WP * HP * RS;    // bytes: [HP][RS1]
   static constexpr int O_X = O_W1 + HP * RS1;         // input slots, [waves][64 rows][64 bytes]
   static constexpr int BYTES = O_X + LT / 64 * 64 * 64;
 };
 
-// exponent e with |x| < 2^e, within +-100 (0 for 0)
-__device__ __forceinline__ int expo(float x) {
-  const int e = x > 0.0f ? __builtin_amdgcn_frexp_expf(x) : 0;
-  return e < -100 ? -100 : e > 100 ? 100 : e;
-}
+// exponent e with x < 2^e, x > 0
+__device__ __forceinline__ int expo(float x) { return __builtin_amdgcn_frexp_expf(x); }
 
 template <int HP>
 __device__ void stage_ln(const EvictArgs& a, float* sm) {
@@ -401,8 +409,9 @@ __device__ void stage_ln(const EvictArgs& a, float* sm) {
   constexpr int RS = Y::RS, RS1 = Y::RS1, O_B1 = Y::O_B1, O_B2 = Y::O_B2;
   constexpr int PARTS = LT / HP, PER = HP / PARTS;    // threads per column of W2, rows per thread
   __shared__ double csum[PARTS][HP];
+  __shared__ float cmax[PARTS][HP];
   __shared__ double m1[8];                            // means of W1's columns, of b1 and of b2
-  __shared__ float wmax[3][LT / 64];
+  __shared__ int wtop[LT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h1 = a.h1, h2 = a.h2, nin = a.n_in;
   const float* W1 = a.params;
@@ -438,48 +447,58 @@ __device__ void stage_ln(const EvictArgs& a, float* sm) {
   double mean = csum[0][k];
   for (int q = 1; q < PARTS; ++q) mean += csum[q][k];
   mean /= h2;
-  float mw = 0.0f, mh = 0.0f, mb = 0.0f;
+  float mw = 0.0f;
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int n = part + PARTS * j;
-    w[j] = (k < h1 && n < h2) ? (float)((double)w[j] - mean) : 0.0f;
-    mw = fmaxf(mw, fabsf(w[j]));
+    const float c = (k < h1 && n < h2) ? (float)((double)w[j] - mean) : 0.0f;
+    mw = fmaxf(mw, fabsf(c));
+    if constexpr (Y::WP == 2) w[j] = c;
   }
-  if (tid < h1) mh = __builtin_fmaf(fabsf(g1[tid]), __builtin_sqrtf((float)h1), fabsf(be1[tid]));
-  if (tid < h2) mb = fabsf((float)((double)b2[tid] - m1[6]));
-  for (int m = 32; m >= 1; m >>= 1) {
-    mw = fmaxf(mw, __shfl_xor(mw, m));
-    mh = fmaxf(mh, __shfl_xor(mh, m));
-    mb = fmaxf(mb, __shfl_xor(mb, m));
-  }
-  if (lane == 0) {
-    wmax[0][wave] = mw;
-    wmax[1][wave] = mh;
-    wmax[2][wave] = mb;
-  }
+  cmax[part][k] = mean - mean == 0.0 ? mw : 1.0f;     // (a column with a NaN or an infinity goes through)
+  // unit k's activation is at most mh (none: the ReLU never lets it through)
+  const float mh = k < h1 ? __builtin_fmaf(fabsf(g1[k]), __builtin_sqrtf((float)h1), be1[k]) : 0.0f;
+  const float mb = tid < h2 ? fabsf((float)((double)b2[tid] - m1[6])) : 0.0f;
   __syncthreads();
-  for (int q = 0; q < LT / 64; ++q) {
-    mw = fmaxf(mw, wmax[0][q]);
-    mh = fmaxf(mh, wmax[1][q]);
-    mb = fmaxf(mb, wmax[2][q]);
+  mw = cmax[0][k];
+  for (int q = 1; q < PARTS; ++q) mw = fmaxf(mw, cmax[q][k]);
+  // The largest product h W2 of the network is below 2^top, unit k's below
+  // 2^(top - dk): scaled by 2^(30 - top) in all, half of dk is left to the
+  // activation's scale 2^ek and half to the weights'.  The bias stays below 2^60 (no
+  // variance overflows), and no network is scaled up by more than 2^120.
+  const bool live = mh > 0.0f && mw > 0.0f;
+  const int pk = live ? expo(mh) + expo(mw) : -90;
+  int top = mb > 0.0f && expo(mb) - 30 > pk ? expo(mb) - 30 : pk;
+  top = top < -90 ? -90 : top;
+  for (int m = 32; m >= 1; m >>= 1) {
+    const int o = __shfl_xor(top, m);
+    top = o > top ? o : top;
   }
-  // scales 2^ex, 2^ew: activations and weights below 2^15 (float16 ends at
-  // 65504), and the bias below 2^60 so that no variance overflows
-  const int ex = 15 - expo(mh);
-  int ew = 15 - expo(mw);
-  ew = ew < 60 - ex - expo(mb) ? ew : 60 - ex - expo(mb);
-  ew = ew < -100 - (ex < 0 ? ex : 0) ? -100 - (ex < 0 ? ex : 0) : ew;
-  ew = ex + ew > 120 ? 120 - ex : ew;
+  if (lane == 0) wtop[wave] = top;
+  __syncthreads();
+  for (int q = 0; q < LT / 64; ++q) top = wtop[q] > top ? wtop[q] : top;
+  top = top > 130 ? 130 : top;                        // (products beyond float32: no value either way)
+  const int ek = live ? 15 - ((top - pk) >> 1) - expo(mh) : 0, ew = 30 - top - ek;
   char* w2 = reinterpret_cast<char*>(sm) + Y::O_W2;
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int n = part + PARTS * j;
-    const float x = __builtin_ldexpf(w[j], ew);
-    const _Float16 xh = (_Float16)x;
-    const _Float16 xl = (_Float16)(x - (float)xh);
+    _Float16 xh;
+    float r;                              // what xh leaves
+    if constexpr (Y::WP == 2) {
+      const float x = live ? __builtin_ldexpf(w[j], ew) : 0.0f;
+      xh = (_Float16)x;
+      r = x - (float)xh;
+    } else {                              // from binary64: the centred weight is not rounded first
+      const double x = live && n < h2 ? __builtin_ldexp((double)w[j] - mean, ew) : 0.0;
+      xh = (_Float16)(float)x;
+      r = (float)(x - (double)xh);
+    }
+    const _Float16 xl = (_Float16)r;
     const int q = (2 * w2_pos(k)) ^ (16 * (n & Y::CM));
     *reinterpret_cast<_Float16*>(w2 + n * RS + q) = xh;
     *reinterpret_cast<_Float16*>(w2 + (HP + n) * RS + q) = xl;
+    if constexpr (Y::WP == 3) *reinterpret_cast<_Float16*>(w2 + (2 * HP + n) * RS + q) = (_Float16)(r - (float)xl);
   }
   char* w1 = reinterpret_cast<char*>(sm) + Y::O_W1;
   for (int e = tid; e < HP * 8; e += LT) {            // unit e / 8, input e % 8 (five of them)
@@ -496,17 +515,18 @@ __device__ void stage_ln(const EvictArgs& a, float* sm) {
       *reinterpret_cast<__bf16*>(row + ((2 * (30 + x - 5)) ^ sw)) = (__bf16)0.0f;
     }
   }
-  for (int i = tid; i < HP; i += LT) {
+  if (tid < HP) {                                     // (unit k = tid)
+    const int i = tid;
     const bool v2 = i < h2, v1 = i < h1;
     sm[O_B1 + i] = v1 ? (float)((double)b1[i] - m1[5]) : 0.0f;
-    sm[O_B1 + HP + i] = v1 ? __builtin_ldexpf(g1[i], ex) : 0.0f;
-    sm[O_B1 + 2 * HP + i] = v1 ? __builtin_ldexpf(be1[i], ex) : 0.0f;
-    sm[O_B2 + i] = v2 ? __builtin_ldexpf((float)((double)b2[i] - m1[6]), ex + ew) : 0.0f;
+    sm[O_B1 + HP + i] = live ? __builtin_ldexpf(g1[i], ek) : 0.0f;
+    sm[O_B1 + 2 * HP + i] = live ? __builtin_ldexpf(be1[i], ek) : 0.0f;
+    sm[O_B2 + i] = v2 ? __builtin_ldexpf((float)((double)b2[i] - m1[6]), 30 - top) : 0.0f;
     sm[O_B2 + HP + i] = v2 ? g2[i] : 0.0f;
     sm[O_B2 + 2 * HP + i] = v2 ? be2[i] : 0.0f;
     sm[O_B2 + 3 * HP + i] = v2 ? wo[i] : 0.0f;
   }
-  if (tid == 0) sm[Y::O_C] = __builtin_ldexpf(1.0f, -(ex + ew));
+  if (tid == 0) sm[Y::O_C] = __builtin_ldexpf(1.0f, top - 30);
 }
 
 // x - xh rounded to float16 for both halves of xh (one mixed-precision
@@ -597,12 +617,22 @@ score_ln2_kernel(EvictArgs a, uint64_t* keys, int kstride, int nq) {
       const lchar* w1 = (const lchar*)sm + Y::O_W1 + ri * RS1 + 16 * (kg ^ swz64(ri));
       asm volatile("" : "+v"(p1), "+v"(w1));
       const bf16x8_t xs = *reinterpret_cast<lbf16x8*>(xr);
+      // (narrow networks: the products of the high parts onto the sum of the others)
+      bf16x8_t x0 = xs, x1 = {};
+      if constexpr (Y::WP == 3) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+          x1[i] = kg == 0 ? xs[i] : (__bf16)0.0f;
+          x0[i] = kg == 0 ? (__bf16)0.0f : xs[i];
+        }
+      }
       f32x4_v hv[NB];
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         const bf16x8_t wv = *reinterpret_cast<lbf16x8*>(w1 + 16 * b * RS1);
         const f32x4_v c0 = *reinterpret_cast<lfloat4*>(p1 + O_B1 + 16 * b);
-        hv[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, xs, c0, 0, 0, 0);
+        hv[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, x0, c0, 0, 0, 0);
+        if constexpr (Y::WP == 3) hv[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, x1, hv[b], 0, 0, 0);
       }
       float s2 = 0.0f;
 #pragma unroll
@@ -643,6 +673,10 @@ score_ln2_kernel(EvictArgs a, uint64_t* keys, int kstride, int nq) {
         for (int t = 0; t < NT; ++t) {
           wh[t] = *reinterpret_cast<lf16x8*>(w2[t] + 16 * b * RS);
           const f16x8_t wl = *reinterpret_cast<lf16x8*>(w2[t] + (HP + 16 * b) * RS);
+          if constexpr (Y::WP == 3) {
+            const f16x8_t wn = *reinterpret_cast<lf16x8*>(w2[t] + (2 * HP + 16 * b) * RS);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(wn, ah[t], c, 0, 0, 0);
+          }
           c = __builtin_amdgcn_mfma_f32_16x16x32_f16(wl, al[t], c, 0, 0, 0);
           c = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh[t], al[t], c, 0, 0, 0);
           c = __builtin_amdgcn_mfma_f32_16x16x32_f16(wl, ah[t], c, 0, 0, 0);

@@ -173,9 +173,15 @@ LN_CASES = [((128, 128), 5, 3, 70, "plain"), ((64, 64), 4, 3, 17, "plain"), ((10
             ((64, 40), 5, 2100, 100, "plain"), ((128, 128), 5, 3, 70, "w2 1e18"),
             ((128, 128), 5, 3, 70, "w2 1e-18"), ((128, 128), 5, 3, 70, "gain 1e6"),
             ((64, 64), 5, 3, 70, "bias 1e6"), ((128, 128), 5, 3, 70, "b2 1e12"), ((96, 96), 5, 3, 70, "w2 0")]
+# Hidden units of very different size, each with a scale of its own: one gain (and
+# shift) of 1e6 or 1e8 with its outgoing weights divided by the same, gains spread over
+# nine decades so, a unit of large gain that its shift keeps switched off, and one
+# whose outgoing weights outweigh all others where it is on.
+UNEVEN = [(h, n, 3, 150, k) for h, n in (((128, 128), 5), ((64, 64), 4), ((100, 77), 5), ((32, 32), 4))
+          for k in ("unit 1e6", "unit 1e8", "spread 1e9", "off 1e6", "out 1e3")]
 
 
-@pytest.mark.parametrize("hidden,n_in,units,L,scale", LN_CASES)
+@pytest.mark.parametrize("hidden,n_in,units,L,scale", LN_CASES + UNEVEN)
 def test_layer_norm_network_scores(hidden, n_in, units, L, scale):
     buf = DecodeBuffers(units, 1, 1, 1, 64, L + 1, "bf16", 8, 0.0, True, sigma=True)
     buf.reserve_workspace(L + 1)
@@ -201,6 +207,20 @@ def test_layer_norm_network_scores(hidden, n_in, units, L, scale):
         p[o_b1:o_b1 + h1] += 1e6
     if scale == "b2 1e12":
         p[o_b2:o_b2 + h2] *= 1e12
+    kind, size = scale.split()[0], float(scale.split()[-1]) if scale != "plain" else 1.0
+    uneven = kind in ("unit", "spread", "off", "out")
+    if uneven:
+        gain, shift, w2 = p[o_b1 + h1:o_b1 + 2 * h1], p[o_b1 + 2 * h1:o_w2], p[o_w2:o_b2].reshape(h2, h1)
+        c = np.where(np.arange(h1) == 3, size, 1.0) if kind != "spread" else size ** (np.arange(h1) / (h1 - 1.0))
+        if kind != "out":
+            gain *= c
+            shift *= c
+        if kind in ("unit", "spread"):
+            w2 /= c
+        if kind == "off":
+            shift[3] = -40.0 * size
+        if kind == "out":
+            w2 *= c
     p = p.astype(np.float32)
     params = torch.from_numpy(p).cuda()
     scores = torch.empty((units, L), dtype=torch.float32, device="cuda")
@@ -219,3 +239,13 @@ def test_layer_norm_network_scores(hidden, n_in, units, L, scale):
         tol = 64 * 2.0 ** -23 * (np.abs(wo) * (np.abs(g2) * np.sqrt(h2) + np.abs(be2))).sum() + 2.0 ** -20
         err = np.abs(scores[u].double().cpu().numpy() - ref)
         assert np.all(np.isfinite(err)) and err.max() <= tol, (u, err.max(), tol)
+        if uneven:
+            # against the same float32 inputs, rms: the rounding of a normalised unit, 16
+            # halves of a float32 digit, independent from unit to unit (7 at most seen;
+            # 60 and more with one scale for all units)
+            x[:, -2:] = np.stack([x[:, -2].astype(np.float32),
+                                  at(buf.pos).astype(np.float32) * (np.float32(1) / np.float32(2 * L))], axis=1)
+            err = scores[u].double().cpu().numpy() - opol.scores(p, x, hidden, layer_norm=True)
+            rms, one = np.sqrt(np.mean(err ** 2)), np.sqrt((wo ** 2 * (g2 ** 2 + be2 ** 2)).sum())
+            print(f"rms error {rms / one * 2 ** 24:.2f} halves of a digit", flush=True)
+            assert rms <= 16 * 2.0 ** -24 * one, (u, rms, one)
