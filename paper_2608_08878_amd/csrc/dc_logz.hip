@@ -47,6 +47,14 @@
 // B t enters the result only by the rows that the sum over x > 0 does not already
 // count, so a t in the middle of a wide gap costs no digits.
 //
+// Two to eight rows kept or evicted: e_K itself, the rows' factors 1 + w z multiplied
+// up as far as z^8 (KF fused multiply-adds a row; every term is positive).  Where the K
+// rows lie so far apart that the product underflows, the factors q + p z behind t.
+// Measured (2048 units, K = 2 and 8): 1025 rows 13 and 19 us, 8193 rows 33 and 39; by
+// the nodes above 41 and 43, 110 and 118; by the recursion in binary32 14 and 25, 74 and
+// 97.  (That one was also faster for nine rows and more of very short units: 2048 units
+// of 65 rows, 16 of them, 13 us against 33 here; of 257 rows 33 and 36.)
+//
 // One row kept or one row evicted (K = 1, the steady step) is a logsumexp over
 // the rows and skips all this.
 // Measured (2048 units of 2049 rows): 18-22 us, all of it latency (33 MB are
@@ -292,11 +300,64 @@ __device__ __forceinline__ Cplx cmul(const Cplx& x, const Cplx& y) {
   return {__builtin_fma(x.re, y.re, -(x.im * y.im)), __builtin_fma(x.re, y.im, x.im * y.re)};
 }
 
-// ONE: at most one row is kept or evicted in every unit (the host knows): the
-// characteristic function's registers and LDS are left out.
-template <int NT, bool ONE>
+// e = e o of two polynomials, up to z^KF
+template <int KF>
+__device__ __forceinline__ void poly_mul(double (&e)[KF + 1], const double (&o)[KF + 1]) {
+#pragma unroll
+  for (int j = KF; j >= 0; --j) {
+    double v = e[j] * o[0];
+#pragma unroll
+    for (int i = 0; i < j; ++i) v = __builtin_fma(e[i], o[j - i], v);
+    e[j] = v;
+  }
+}
+
+// The product over the block of the threads' polynomials (fixed order), for every
+// thread; buf: (KF + 1) NT / 64 doubles.
+template <int NT, int KF>
+__device__ __forceinline__ void poly_red(double (&e)[KF + 1], double* buf) {
+  constexpr int NW = NT / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double o[KF + 1];
+#define DC_STEP(CTRL)                                    \
+  _Pragma("unroll") for (int j = 0; j <= KF; ++j) o[j] = dppd<CTRL>(e[j]); \
+  poly_mul<KF>(e, o);
+  DC_STEP(DPP_XOR1)
+  DC_STEP(DPP_XOR2)
+  DC_STEP(DPP_HALF_MIRROR)
+  DC_STEP(DPP_MIRROR)
+#undef DC_STEP
+  // the four rows of lanes, then the waves (a wave's lanes past NW repeat its last)
+  double r[KF + 1];
+#pragma unroll
+  for (int j = 0; j <= KF; ++j) r[j] = lane_of(e[j], 0);
+#pragma unroll
+  for (int q = 16; q < 64; q += 16) {
+#pragma unroll
+    for (int j = 0; j <= KF; ++j) o[j] = lane_of(e[j], q);
+    poly_mul<KF>(r, o);
+  }
+  __syncthreads();
+  if (lane == 0)
+#pragma unroll
+    for (int j = 0; j <= KF; ++j) buf[wave * (KF + 1) + j] = r[j];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j <= KF; ++j) e[j] = buf[j];
+  for (int w = 1; w < NW; ++w) {
+#pragma unroll
+    for (int j = 0; j <= KF; ++j) o[j] = buf[w * (KF + 1) + j];
+    poly_mul<KF>(e, o);
+  }
+}
+
+// KF = 0: any budgets.  KF = 1: at most one row is kept or evicted in every unit (the
+// host knows), 4 and 8: two to KF of them; the characteristic function's registers and
+// LDS are left out.
+template <int NT, int KF>
 __global__ void __launch_bounds__(NT, 4) logz_kernel(LogzArgs a) {
   constexpr int NW = NT / 64;
+  constexpr bool ONE = KF == 1;
   __shared__ double red[3 * NW];
   __shared__ double zpow[NMAX][8];        // z, z^2, z^3, z^4 of every node
   __shared__ double2 co[2][CHUNK / 4];
@@ -367,7 +428,7 @@ __global__ void __launch_bounds__(NT, 4) logz_kernel(LogzArgs a) {
     finish(sum);
     return;
   }
-  if (ONE || B == 1 || L - B == 1) {
+  if (ONE || (KF == 0 && (B == 1 || L - B == 1))) {
     // one row kept: log sum e^r; one row evicted: sum r + log sum e^-r
     const bool one = B == 1;
     const double c = one ? mx : -mn;
@@ -398,7 +459,62 @@ __global__ void __launch_bounds__(NT, 4) logz_kernel(LogzArgs a) {
     finish((one ? 0.0 : sum) + c + log(e[0]));
     return;
   }
-  if constexpr (!ONE) {
+  if constexpr (KF > 1) {
+    // few rows kept or few evicted: e_K of the weights relative to the largest, by
+    // multiplying up the rows' factors 1 + w z as far as z^KF
+    __shared__ double buf[(KF + 1) * NW];
+    const bool neg = L - B < B;
+    const int K = neg ? L - B : B;
+    const double c = neg ? -mn : mx;
+    double e[KF + 1] = {1.0};
+    auto kth = [&]() {
+      double v = 0.0;                       // (a sum: a chosen element would put e in memory)
+#pragma unroll
+      for (int j = 2; j <= KF; ++j) v = __builtin_fma(K == j ? 1.0 : 0.0, e[j], v);
+      return v;
+    };
+    auto add = [&](float x) {
+      const double r = (double)x * itau, w = exp_neg((neg ? -r : r) - c);
+#pragma unroll
+      for (int j = KF; j > 0; --j) e[j] = __builtin_fma(w, e[j - 1], e[j]);
+    };
+#pragma unroll
+    for (int j = 0; j < KR; ++j)
+      if (tid + j * NT < L) add(keep[j]);
+#pragma unroll 2
+    for (int i = tid + KR * NT; i < L; i += NT) add(s[i]);
+    poly_red<NT, KF>(e, buf);
+    if (kth() > 1e-250 && !(neg && c > MASK_R)) {
+      finish((neg ? sum : 0.0) + K * c + log(kth()));
+      return;
+    }
+    // the K rows are far from the largest, or a sum over masked rows would lose
+    // digits: the factors q + p z of the trials behind t
+    Search f = {mx, sum / L - mx - log((double)B / (double)(L - B)), 0.0, 0.0, false};
+    moments<NT>(s, L, itau, mx, f.t, red, f.mean, f.var);
+    f.found = close_to(f.mean, f.var, B);
+    if (!f.found) f = search<NT>(s, L, B, itau, mx, mn, f.t, f.mean, red);
+#pragma unroll
+    for (int j = 0; j <= KF; ++j) e[j] = j == 0 ? 1.0 : 0.0;
+    double v[3] = {0.0, 0.0, 0.0};        // sum of r over x > 0, of log(1 + e^-|x|), rows with x > 0
+    for (int i = tid; i < L; i += NT) {
+      const double r = (double)s[i] * itau, x = (r - f.ref) - f.t;
+      const double g = exp_neg(-fabs(x)), hi = 1.0 / (1.0 + g), lo = g * hi;
+      const double w1 = (x >= 0.0) == neg ? lo : hi, w0 = (x >= 0.0) == neg ? hi : lo;
+#pragma unroll
+      for (int j = KF; j > 0; --j) e[j] = __builtin_fma(w1, e[j - 1], w0 * e[j]);
+      e[0] *= w0;
+      v[0] += x > 0.0 ? r : 0.0;
+      v[1] += log(1.0 + g);
+      v[2] += x > 0.0 ? 1.0 : 0.0;
+    }
+    poly_red<NT, KF>(e, buf);
+    block_red<NT, 3>(v, Add(), red);
+    const bool ok = f.found && kth() > 0.0;
+    finish(ok ? v[0] + ((double)B - v[2]) * (f.ref + f.t) + v[1] + log(kth()) : __builtin_nan(""));
+    return;
+  }
+  if constexpr (KF == 0) {
 
   // t, relative to ref: E[S] within a quarter of a standard deviation of B is
   // enough, so binary32 weights do.  Newton on logit(E[S] / L), exact in one step
@@ -578,7 +694,7 @@ size_t logz_ws_bytes(int units, int L, int B) {
 int launch_logz(const LogzArgs& a, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   const bool uniform = !a.unit_len && !a.budgets;
-  const bool one = uniform && (a.B >= a.L || a.B == 1 || a.L - a.B == 1);
+  const int K = a.L - a.B < a.B ? a.L - a.B : a.B;
   // At most one unit per CU: 1024 threads each, so that a unit's rows go by faster
   // (256 units of 8193 rows 30.6 us; 257 in 256 threads each 34.4 us); beyond, a
   // CU holds one such workgroup at a time (511 units 68 us, in 256 threads 37 us).
@@ -586,10 +702,14 @@ int launch_logz(const LogzArgs& a, void* stream) {
   auto launch = [&](auto kern, int nt) {
     hipLaunchKernelGGL(kern, dim3(a.units), dim3(nt), 0, s, a);
   };
-  if (one && wide) launch(logz_kernel<1024, true>, 1024);
-  else if (one) launch(logz_kernel<256, true>, 256);
-  else if (wide) launch(logz_kernel<1024, false>, 1024);
-  else launch(logz_kernel<256, false>, 256);
+  // (the polynomials of 2-8 rows spill at 1024 threads: 8 units of 8193 rows, 8 evicted,
+  // 20 us, 300 units in 256 threads each 14)
+  if (uniform && K <= 1 && wide) launch(logz_kernel<1024, 1>, 1024);
+  else if (uniform && K <= 1) launch(logz_kernel<256, 1>, 256);
+  else if (uniform && K <= 4) launch(logz_kernel<256, 4>, 256);
+  else if (uniform && K <= 8) launch(logz_kernel<256, 8>, 256);
+  else if (wide) launch(logz_kernel<1024, 0>, 1024);
+  else launch(logz_kernel<256, 0>, 256);
   return (int)hipGetLastError();
 }
 

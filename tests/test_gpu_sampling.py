@@ -100,7 +100,11 @@ def test_log_partition_workload_sizes(units, L, B_, tau):
 EDGES = [(2, 2, 1, 1.0), (2, 3, 2, 1.0), (2, 4, 2, 1.0), (2, 5, 3, 4000.0), (2, 61, 30, 0.3),
          (2, 64, 32, 1.0), (300, 67, 20, 2.0), (300, 257, 255, 1.0), (2, 513, 100, 3000.0),
          (2, 1000, 4, 12.0), (1, 4096, 40, 1.0), (1, 4097, 4000, 1.0), (1, 8193, 60, 0.1),
-         (257, 300, 1, 1.0), (257, 300, 299, 800.0)]
+         (257, 300, 1, 1.0), (257, 300, 299, 800.0),
+         # two to eight rows kept or evicted, in both workgroup sizes, and so far apart
+         # that the weights relative to the largest underflow
+         (300, 257, 8, 1.0), (300, 513, 505, 1.0), (3, 2100, 2095, 1.0), (3, 2100, 8, 1.0), (3, 300, 7, 1.0),
+         (3, 9, 4, 1.0), (2, 300, 6, 4000.0), (300, 300, 294, 4000.0), (2, 2500, 8, 4000.0)]
 
 
 @pytest.mark.parametrize("units,L,B_,scale", EDGES)
