@@ -1128,10 +1128,15 @@ int step_ragged_rows(int G, int D) {
   return L;
 }
 
-// One workgroup per CU at most (G > 4: its registers allow no second), or more
-// rounds than one of not too long rows (step_unit_body's comment has both sides).
-static bool step_early(const DecodeArgs& a, int G) {
-  return G > 4 || a.units <= 256 || a.L <= 512 || (a.units > 512 && a.L <= 3584);
+// One workgroup per CU at most (G > 4: its registers allow no second), or more rounds
+// than one of not too long rows.  Measured on / off, 17 unit counts by nine lengths by
+// five shapes: up to 256 units 0.82-1.00 everywhere; G = 8 0.83-0.98 everywhere; over
+// 512 units 0.77-0.99 to 2049 rows, 0.94-1.01 at 3001, 0.95-1.005 from 3585; 257-512
+// units with rows of 128 elements 0.97-1.00 at 129 rows, 0.98-1.05 from 257 to 1025, then
+// 0.98-1.00 (with rows of 64 0.85-1.00).
+static bool step_early(const DecodeArgs& a, int G, int D) {
+  if (G > 4 || a.units <= 256) return true;
+  return a.units > 512 ? a.L <= 3584 : a.L <= (D > 64 ? 192 : 512);
 }
 
 template <int D, int G>
@@ -1150,7 +1155,7 @@ static int launch_step_t(const DecodeArgs& a, const EvictArgs* e, bool feat, boo
       hipLaunchKernelGGL(kern, dim3(a.units), dim3(SNT), lds, s, a, ee);
     };
     // (the fused evicting variants serve the one-hidden-layer four-input policy)
-    const bool early = step_early(a, G);
+    const bool early = step_early(a, G, D);
 #define DC_STEP(...) do { if (early) pick(step_unit_kernel<D, G, __VA_ARGS__, true>); else pick(step_unit_kernel<D, G, __VA_ARGS__, false>); } while (0)
     if (!feat) DC_STEP(false, false, false, false, false);
     else if (e && e->sample) {
@@ -1213,7 +1218,7 @@ static int launch_step_mixed_t(const DecodeArgs& a, const EvictArgs& e, const De
     allow_lds((const void*)kern, lds);
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.units * (1 + ac.nchunks))), dim3(SNT), lds, s, a, e, ac);
   };
-  const bool early = step_early(a, G);
+  const bool early = step_early(a, G, D);
   if (ac.retire) early ? pick(step_mixed_kernel<D, G, true, true>) : pick(step_mixed_kernel<D, G, true, false>);
   else early ? pick(step_mixed_kernel<D, G, false, true>) : pick(step_mixed_kernel<D, G, false, false>);
   for_grid_y(ac.units, [&](int y0, int ny) {
