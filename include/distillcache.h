@@ -180,7 +180,11 @@ dc_status dc_feat_init(const dc_dims *dims, const dc_kv *kv, dc_feat *feat, int3
  * not NULL (per-row scratch between the key and feature passes), and for
  * plain attention over caches longer than fit on chip.
  * Errors: DC_ERR_NULL, DC_ERR_SHAPE (len == 0 without append, len > capacity),
- * DC_ERR_CAPACITY (len + 1 > capacity), DC_ERR_UNSUPPORTED, DC_ERR_WORKSPACE. */
+ * DC_ERR_CAPACITY (len + 1 > capacity), DC_ERR_UNSUPPORTED, DC_ERR_WORKSPACE.
+ * A feature step on few bf16 units (under 128) is cut into chunks of rows where that is
+ * faster and ws_bytes covers the size above; a smaller workspace that holds the scratch
+ * of a single launch takes that launch, whose results differ in the last bits.
+ */
 dc_status dc_decode_step(const dc_dims *dims, dc_kv *kv, dc_feat *feat, const void *q,
                          const void *k_new, const void *v_new, void *out, void *ws,
                          size_t ws_bytes, void *hip_stream);
@@ -325,7 +329,8 @@ dc_status dc_decode_sample_evict(const dc_dims *dims, dc_kv *kv, dc_feat *feat,
  * large finite score cost no digits as long as subsets without them exist).  A
  * non-finite score or a kept index outside [0, len) gives NaN for that unit.
  * Workspace: dc_subset_log_prob_workspace_bytes(units, len, budget) bytes
- * (zero unless K > 4096).
+ * (zero unless K = min(budget, len - budget) > 4096).  Required and checked, but no
+ * longer read: any device memory of that size serves.
  * Errors: DC_ERR_NULL (scores, or kept with logp_out), DC_ERR_SHAPE (units or
  * len < 1), DC_ERR_BUDGET, DC_ERR_VALUE (tau), DC_ERR_UNSUPPORTED (len > 40960,
  * units > 2^24), DC_ERR_WORKSPACE. */

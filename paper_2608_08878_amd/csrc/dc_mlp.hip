@@ -356,7 +356,7 @@ score_mlp2_kernel(EvictArgs a, uint64_t* keys, int kstride) {
 // 4097 rows, 64-64: 191 -> 223 us; six bf16 products 306).
 //
 // What bounds it: the sum of matrix and vector instructions, which do not overlap
-// on a SIMD here (counters: 559 k MFMA cycles + 500 k vector cycles of 1067 k; a
+// on a SIMD here (counters: 559 k MFMA cycles + 417 k vector cycles of 993 k; a
 // probe with one wave of each agrees).  So the vector work is cut: a lane per
 // row forms the inputs of 64 rows at a time, the means come out of the matrix
 // product, a float16 residual is one mixed-precision instruction, and both layers'
@@ -364,7 +364,7 @@ score_mlp2_kernel(EvictArgs a, uint64_t* keys, int kstride) {
 // reads) changed nothing, three products instead of four would save 55 us.
 // One workgroup per CU stages the weights once and strides over all units' rows.
 // Measured (1024 units x 4097 rows, 5 -> 128 -> 128 -> 1): 517-585 us against
-// 890-950 us with the bf16 split of six products; the whole step with decode, global
+// 748-950 us with the bf16 split of six products; the whole step with decode, global
 // alpha and selection 1234 -> 962 us.
 constexpr int LT = 1024;                              // threads: one workgroup per CU, four waves per SIMD
 

@@ -1,6 +1,6 @@
 """GPU parity at the documented maximum sizes: a 40960-row cache (the largest
 the selection takes) through decode and a compression step, and the exact
-log-partition at 40960 rows with K = 20480 (five bands of the recursion)."""
+log-partition at 40960 rows with K = 20480 (ten chunks of rows)."""
 import numpy as np
 import pytest
 import torch
