@@ -73,7 +73,7 @@ def test_log_partition_small_rows(B_, tau):
 
 
 # (units, L, B, tau): one eviction per step, a 64-token block, compression steps
-# of the decode workloads, two bands (K > 4096) and the largest single band.
+# of the decode workloads, K above and at 4096 (the workspace rule).
 LARGE = [(4, 2049, 2048, 1.0), (2, 3341, 3277, 1.0), (2, 4097, 1024, 1.0), (2, 8193, 2048, 1.0),
          (1, 9000, 4500, 0.8), (1, 16385, 4096, 1.0), (1, 12000, 11990, 1.3)]
 
